@@ -1,0 +1,408 @@
+"""Performance cases of the ensemble-inference path on one GPU.
+
+Two public entry points carry a program's work.  A server creates an ensemble
+once and sends it requests: `fs_infer_device` on images that are already in
+device memory, `fs_infer` on host images.  A program that brings its own
+tensors runs single convolution layers with `fs_conv_bf16_device_noalloc`.
+The cases are such calls at the sizes of this repository's configurations:
+ResNet-18, ResNet-50, VGG-11 and a tiny net, batches of 1 to 256, images of
+160 to 320 pixels a side.
+
+Images are smooth colour fields with noise on top, as photographs are mostly
+smooth; weights are He-normal, with batch-norm scales and shifts, since no
+trained ones exist here.  Two things follow what trained classifiers do: the
+head's weights are small enough for logits with a spread of about one, and
+the models of an ensemble agree on a class, by a bias of the head, so that the
+class outputs are decided by more than a rounding.
+
+The weights belong to the ensemble and are the same for every seed (a server
+keeps them); the images and the layers' tensors come from the seed.
+"""
+import ctypes
+import functools
+import math
+
+import torch
+
+from paper_2003_01538_amd import flexserve as fsv
+
+MEAN = (0.485, 0.456, 0.406)
+STD = (0.229, 0.224, 0.225)
+TOP_CLASS = 7        # the class that the ensemble's models agree on
+TOP_BIAS = 4.0       # ... and the bias that its logit gets
+
+# (cin, cout, kernel, stride, height = width of the input, residual): the
+# convolution layers of ResNet-18, ResNet-50 and VGG-11 with 64 channels or
+# more at their 224 x 224 sizes.
+LAYERS = (
+    (64, 64, 3, 1, 56, 1), (64, 128, 3, 2, 56, 0), (128, 128, 3, 1, 28, 1), (128, 256, 3, 2, 28, 0),
+    (256, 256, 3, 1, 14, 1), (256, 512, 3, 2, 14, 0), (512, 512, 3, 1, 7, 1), (64, 256, 1, 1, 56, 1),
+    (256, 64, 1, 1, 56, 0), (256, 128, 1, 1, 56, 0), (128, 512, 1, 1, 28, 1), (512, 128, 1, 1, 28, 0),
+    (256, 1024, 1, 1, 14, 1), (1024, 256, 1, 1, 14, 0), (512, 2048, 1, 1, 7, 1), (2048, 512, 1, 1, 7, 0),
+    (64, 128, 3, 1, 112, 0), (256, 256, 3, 1, 56, 0), (512, 512, 3, 1, 28, 0), (512, 512, 3, 1, 14, 0),
+)
+
+
+# ------------------------------------------------------------------ cases
+def _ensemble(name, models, dtype, batch, lo, hi, where="device", combine="mean", out=224):
+    """One request: `batch` images of lo..hi pixels a side, resized to `out`."""
+    return {"name": name, "kind": "ensemble", "models": models, "dtype": dtype, "batch": batch, "lo": lo,
+            "hi": hi, "where": where, "combine": combine, "out": out}
+
+
+def _layer(name, batch, cin, cout, k, stride, h, w, residual):
+    return {"name": name, "kind": "conv", "batch": batch, "cin": cin, "cout": cout, "k": k, "stride": stride,
+            "h": h, "w": w, "residual": residual}
+
+
+def listed():
+    return [
+        # the smallest configuration: two tiny fp32 nets, four 32 x 32 images; launches are all its time
+        _ensemble("tiny2_fp32_b4", "tiny*2", "fp32", 4, 32, 32, out=32),
+        # one image through the quoted ensemble: the latency of an interactive request
+        _ensemble("r18x3_bf16_b1", "resnet18*3", "bf16", 1, 256, 256),
+        # a small ragged request, classes by plurality
+        _ensemble("r18x3_bf16_b7_ragged", "resnet18*3", "bf16", 7, 160, 320, combine="plurality"),
+        # the quoted configuration: three ResNet-18s, 32 images of 256 x 256
+        _ensemble("r18x3_bf16_b32", "resnet18*3", "bf16", 32, 256, 256),
+        # an odd request of the stream, from host images to host results
+        _ensemble("r18x3_bf16_b31_host", "resnet18*3", "bf16", 31, 160, 320, where="host"),
+        # different architectures side by side
+        _ensemble("r18_r50_vgg11_bf16_b32", "resnet18+resnet50+vgg11", "bf16", 32, 224, 224),
+        # the largest configuration: offline scoring of a big batch
+        _ensemble("r50x5_bf16_b256", "resnet50*5", "bf16", 256, 224, 224),
+        # the fp32 storage mode on a real network
+        _ensemble("r18x3_fp32_b8", "resnet18*3", "fp32", 8, 256, 256),
+        # single layers of a caller's own program: a late layer for one image,
+        _layer("conv3x3_512_7_b1", 1, 512, 512, 3, 1, 7, 7, 1),
+        # a stride-2 entry with an odd batch and an odd map,
+        _layer("conv3x3s2_256_512_15x13_b5", 5, 256, 512, 3, 2, 15, 13, 0),
+        # a middle layer with its residual,
+        _layer("conv3x3_128_28_b32", 32, 128, 128, 3, 1, 28, 28, 1),
+        # a bottleneck's expansion, bound by memory
+        _layer("conv1x1_64_256_56_b32", 32, 64, 256, 1, 1, 56, 56, 1),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return max(lo, min(hi, int(round(math.exp(rng.uniform(math.log(lo), math.log(hi + 0.49)))))))
+
+
+def draw(rng):
+    kind = rng.choice(("ensemble", "ensemble", "fp32", "conv", "conv"))
+    if kind == "conv":
+        cin, cout, k, stride, hw, res = rng.choice(LAYERS)
+        b = _log_int(rng, 1, 32)
+        h, w = hw, hw
+        if rng.random() < 0.4:  # a map of another size than 224 x 224 images give
+            h, w = max(3, hw + rng.randint(-3, 3)), max(3, hw + rng.randint(-3, 3))
+        c = _layer("", b, cin, cout, k, stride, h, w, res)
+    elif kind == "fp32":
+        if rng.random() < 0.4:
+            c = _ensemble("", "tiny*%d" % rng.randint(1, 3), "fp32", _log_int(rng, 1, 64), 24, 48, out=32)
+        else:
+            c = _ensemble("", "resnet18*%d" % rng.randint(1, 3), "fp32", _log_int(rng, 1, 8), 160, 320)
+    else:
+        models = rng.choice(("resnet18*3", "resnet18*3", "resnet18*1", "resnet18*2", "resnet50*1", "resnet50*5",
+                             "resnet18+resnet50", "resnet18+resnet50+vgg11"))
+        lo = rng.choice((160, 224, 256))
+        c = _ensemble("", models, "bf16", _log_int(rng, 1, 64), lo, 320 if lo == 160 else lo,
+                      where=rng.choice(("device", "device", "host")), combine=rng.choice(("mean", "plurality")))
+    del c["name"]
+    return c
+
+
+# ------------------------------------------------------- nets and weights
+def _conv(src, cin, cout, k, stride, pad, relu, res=-1, bn=True):
+    return dict(op="conv", src=src, res=res, cin=cin, cout=cout, k=k, stride=stride, pad=pad, relu=int(relu), bn=bn)
+
+
+def _fc(src, cin, cout, relu=0, flatten=False):
+    return dict(op="fc", src=src, cin=cin, cout=cout, relu=relu, flatten_nchw=flatten)
+
+
+def _pool(src, k, stride, pad):
+    return dict(op="maxpool", src=src, k=k, stride=stride, pad=pad)
+
+
+def _net(arch):
+    """Layer list of an architecture (the form that flexserve.Ensemble takes)."""
+    if arch == "tiny":
+        return [_conv(-1, 3, 16, 3, 1, 1, True, bn=False), _pool(0, 2, 2, 0), _conv(1, 16, 32, 3, 1, 1, True, bn=False),
+                dict(op="gap", src=2), _fc(3, 32, 10)]
+    if arch == "vgg11":
+        L, x, cin = [], -1, 3
+        for v in (64, 0, 128, 0, 256, 256, 0, 512, 512, 0, 512, 512, 0):
+            L.append(_conv(x, cin, v, 3, 1, 1, True, bn=False) if v else _pool(x, 2, 2, 0))
+            x, cin = len(L) - 1, v or cin
+        L += [_fc(x, 512 * 49, 4096, 1, True), _fc(x + 1, 4096, 4096, 1), _fc(x + 2, 4096, 1000)]
+        return L
+    L = [_conv(-1, 3, 64, 7, 2, 3, True), _pool(0, 3, 2, 1)]
+    x, cin = 1, 64
+    deep = arch == "resnet50"
+    for stage, (width, blocks) in enumerate(zip((64, 128, 256, 512), (3, 4, 6, 3) if deep else (2, 2, 2, 2))):
+        out = width * 4 if deep else width
+        for block in range(blocks):
+            s = 2 if stage and not block else 1
+            if deep:
+                L.append(_conv(x, cin, width, 1, 1, 0, True))
+                L.append(_conv(len(L) - 1, width, width, 3, s, 1, True))
+            else:
+                L.append(_conv(x, cin, width, 3, s, 1, True))
+            last, res = len(L) - 1, x
+            if s != 1 or cin != out:
+                L.append(_conv(x, cin, out, 1, s, 0, False))
+                res = len(L) - 1
+            L.append(_conv(last, width, out, 1 if deep else 3, 1, 0 if deep else 1, True, res=res))
+            x, cin = len(L) - 1, out
+    return L + [dict(op="gap", src=x), _fc(len(L), cin, 1000)]
+
+
+# Scale of the head's weights that gives logits with a spread of about one.
+HEAD_GAIN = {"tiny": 0.7, "resnet18": 0.015, "resnet50": 2e-4, "vgg11": 0.2}
+
+
+@functools.lru_cache(maxsize=8)
+def _model(arch, index):
+    """Net with weights; `index` tells the models of one ensemble apart."""
+    g = torch.Generator().manual_seed(1000 + 31 * index + len(arch))
+    L = [dict(l) for l in _net(arch)]
+    for i, l in enumerate(L):
+        if l["op"] == "conv":
+            l["weight"] = (torch.randn(l["cout"], l["k"], l["k"], l["cin"], generator=g)
+                           * math.sqrt(2.0 / (l["cin"] * l["k"] ** 2))).numpy()
+            if l.pop("bn"):
+                l["bn_scale"] = (0.5 + torch.rand(l["cout"], generator=g)).numpy()
+                l["bn_shift"] = (0.1 * torch.randn(l["cout"], generator=g)).numpy()
+                l["bias"] = None
+            else:
+                l["bn_scale"] = l["bn_shift"] = None
+                l["bias"] = (0.02 * torch.randn(l["cout"], generator=g)).numpy()
+        elif l["op"] == "fc":
+            last = i == len(L) - 1
+            l["weight"] = (torch.randn(l["cout"], l["cin"], generator=g)
+                           * (math.sqrt(2.0 / l["cin"]) * (HEAD_GAIN[arch] if last else 1.0))).numpy()
+            l["bias"] = (0.02 * torch.randn(l["cout"], generator=g)).numpy()
+            if last:
+                l["bias"][TOP_CLASS] += TOP_BIAS
+    return L
+
+
+def _models(text):
+    """"resnet18*3" -> three ResNet-18s, "resnet18+vgg11" -> one of each."""
+    names = []
+    for part in text.split("+"):
+        arch, _, count = part.partition("*")
+        names += [arch] * int(count or 1)
+    return [_model(a, i) for i, a in enumerate(names)]
+
+
+class _Server:
+    """What a serving program creates once: the ensemble and its stream."""
+
+    def __init__(self, models, dtype, out, combine, max_batch):
+        self.ens = fsv.Ensemble(_models(models), (out, out), MEAN, STD, dtype, max_batch=max_batch)
+        if combine == "plurality":
+            self.ens.set_combine(fsv.FS_COMBINE_PLURALITY)
+        self.stream = torch.cuda.Stream()
+
+
+@functools.lru_cache(maxsize=1)
+def _server(models, dtype, out, combine, max_batch):
+    return _Server(models, dtype, out, combine, max_batch)
+
+
+# ------------------------------------------------------------------ inputs
+def _sizes(case, seed):
+    g = torch.Generator().manual_seed(seed)
+    return torch.randint(case["lo"], case["hi"] + 1, (case["batch"], 2), generator=g).tolist()
+
+
+def _images(case, seed):
+    """uint8 HWC images on the GPU: a smooth colour field and noise."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    imgs = []
+    for h, w in _sizes(case, seed):
+        field = torch.rand(1, 3, 6, 6, device="cuda", generator=g) * 255.0
+        field = torch.nn.functional.interpolate(field, size=(h, w), mode="bilinear", align_corners=False)
+        noise = torch.randn(1, 3, h, w, device="cuda", generator=g) * 24.0
+        imgs.append((field + noise).round().clamp(0, 255).to(torch.uint8)[0].permute(1, 2, 0).contiguous())
+    return imgs
+
+
+def _conv_inputs(case, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    b, cin, cout, k = case["batch"], case["cin"], case["cout"], case["k"]
+    ho, wo = _conv_out(case)
+
+    def randn(*shape):
+        return torch.randn(*shape, device="cuda", generator=g)
+
+    x = randn(b, case["h"], case["w"], cin).relu().to(torch.bfloat16)      # behind a ReLU
+    w = (randn(cout, k, k, cin) * math.sqrt(2.0 / (cin * k * k))).to(torch.bfloat16)
+    bias = randn(cout) * 0.1
+    res = randn(b, ho, wo, cout).relu().to(torch.bfloat16) if case["residual"] else None
+    return x, w, bias, res
+
+
+def _conv_out(case):
+    pad = case["k"] // 2
+    return tuple((case[s] + 2 * pad - case["k"]) // case["stride"] + 1 for s in ("h", "w"))
+
+
+def prepare(case, seed):
+    if case["kind"] == "conv":
+        x, w, bias, res = _conv_inputs(case, seed)
+        ho, wo = _conv_out(case)
+        out = torch.empty(case["batch"], ho, wo, case["cout"], device="cuda", dtype=torch.bfloat16)
+        return {"case": case, "x": x, "w": w, "bias": bias, "res": res, "out": out, "call": fsv.load().fs_conv_bf16_device_noalloc}
+    B = case["batch"]
+    # a server's largest pass: 64 images, or the batch of a larger job
+    server = _server(case["models"], case["dtype"], case["out"], case["combine"], max(64, B))
+    imgs = _images(case, seed)
+    s = {"case": case, "server": server}
+    if case["where"] == "host":
+        s["imgs"] = [im.cpu().numpy() for im in imgs]
+        return s
+    desc, off = [], 0  # fs_image_desc as three 64-bit words: offset, h and w, row stride
+    for h, w, _ in (im.shape for im in imgs):
+        desc.append((off, h | (w << 32), 3 * w))
+        off += h * w * 3
+    N, C = server.ens.N, server.ens.C
+    s["pixels"] = torch.cat([im.reshape(-1) for im in imgs])
+    s["desc"] = torch.tensor(desc, dtype=torch.int64, device="cuda")
+    s["out"] = {
+        "probs": torch.empty(N, B, C, device="cuda"), "mean": torch.empty(B, C, device="cuda"),
+        "vote": torch.empty(B, dtype=torch.int32, device="cuda"),
+        "top1": torch.empty(N, B, dtype=torch.int32, device="cuda"), "logits": torch.empty(N, B, C, device="cuda"),
+    }
+    return s
+
+
+def run(s):
+    c = s["case"]
+    if c["kind"] == "conv":
+        res = s["res"]
+        status = s["call"](
+            s["x"].data_ptr(), c["batch"], c["h"], c["w"], c["cin"], s["w"].data_ptr(),
+            ctypes.cast(s["bias"].data_ptr(), ctypes.POINTER(ctypes.c_float)), res.data_ptr() if res is not None else None,
+            c["cout"], c["k"], c["k"], c["stride"], c["k"] // 2, 1, s["out"].data_ptr(),
+            torch.cuda.current_stream().cuda_stream)
+        if status != fsv.FS_OK:
+            raise RuntimeError(fsv.fs_last_error())
+        return s["out"]
+    server = s["server"]
+    if c["where"] == "host":
+        return server.ens.infer(s["imgs"])
+    o = s["out"]
+    fsv.fs_infer_device(server.ens.handle, s["pixels"].data_ptr(), s["desc"].data_ptr(), c["batch"],
+                        o["probs"].data_ptr(), o["mean"].data_ptr(), o["vote"].data_ptr(), o["top1"].data_ptr(),
+                        o["logits"].data_ptr(), server.stream.cuda_stream)
+    return o
+
+
+# -------------------------------------------------------------------- work
+def _shapes(L, hw):
+    out = []
+    for l in L:
+        h, w, c = (hw, hw, 3) if l["src"] < 0 else out[l["src"]]
+        if l["op"] in ("conv", "maxpool"):
+            h, w = ((v + 2 * l["pad"] - l["k"]) // l["stride"] + 1 for v in (h, w))
+            out.append((h, w, l["cout"] if l["op"] == "conv" else c))
+        else:
+            out.append((1, 1, l["cout"] if l["op"] == "fc" else c))
+    return out
+
+
+def work(case):
+    """Images, weights and outputs once; no activation has to leave the chip."""
+    B = case["batch"]
+    if case["kind"] == "conv":
+        ho, wo = _conv_out(case)
+        cin, cout, kk = case["cin"], case["cout"], case["k"] ** 2
+        out = B * ho * wo * cout * 2
+        return {"bytes": B * case["h"] * case["w"] * cin * 2 + cout * kk * cin * 2 + cout * 4 + out * (1 + case["residual"]),
+                "flops": 2.0 * B * ho * wo * cout * kk * cin}
+    flops, weights, n, classes = 0.0, 0, 0, 0
+    for part in case["models"].split("+"):
+        arch, _, count = part.partition("*")
+        count, L = int(count or 1), _net(arch)
+        for l, (h, w, c) in zip(L, _shapes(L, case["out"])):
+            k = l["cin"] * l.get("k", 1) ** 2 if l["op"] in ("conv", "fc") else 0
+            flops += 2.0 * count * B * h * w * c * k
+            weights += count * c * k
+        n, classes = n + count, L[-1]["cout"]
+    side = (case["lo"] + case["hi"]) / 2
+    outputs = B * classes * 4 * (2 * n + 1) + B * 4 * (n + 1)
+    return {"bytes": B * side * side * 3 + weights * (2 if case["dtype"] == "bf16" else 4) + outputs, "flops": flops}
+
+
+def tolerance(case):
+    """About four times the distance from `exact` that was measured."""
+    if case["kind"] == "conv":   # 1.7e-3: the rounding of the outputs to bf16; one step of bf16 is 2^-7
+        return {"rel": 7e-3, "max": 0.02}
+    if case["dtype"] == "fp32":  # 3e-7
+        return {"rel": 2e-6, "max": 2e-5}
+    return {"rel": 0.016, "max": 0.08}  # 4e-3: bf16 activations and weights
+
+
+# ------------------------------------------------------------------- exact
+def _conv64(x, weight, stride, pad):
+    """NHWC convolution in 64 bits: x [B,H,W,Cin], weight [Cout,k,k,Cin]."""
+    cout, k, _, cin = weight.shape
+    if pad:
+        x = torch.nn.functional.pad(x, (0, 0, pad, pad, pad, pad))
+    ho, wo = ((v - k) // stride + 1 for v in x.shape[1:3])
+    y = x.new_zeros(x.shape[0] * ho * wo, cout)
+    for ky in range(k):
+        for kx in range(k):
+            part = x[:, ky:ky + (ho - 1) * stride + 1:stride, kx:kx + (wo - 1) * stride + 1:stride]
+            y.addmm_(part.reshape(-1, cin), weight[:, ky, kx].t())
+    return y.view(x.shape[0], ho, wo, cout)
+
+
+def _logits64(L, x):
+    """A net's logits for x [B, H, W, 3], both in 64 bits."""
+    out, last_use = [], {}
+    for i, l in enumerate(L):
+        last_use[l["src"]] = last_use[l.get("res", -1)] = i
+    for i, l in enumerate(L):
+        v = x if l["src"] < 0 else out[l["src"]]
+        if l["op"] == "conv":
+            wt = torch.from_numpy(l["weight"]).to(x)
+            if l["bn_scale"] is not None:
+                wt = wt * torch.from_numpy(l["bn_scale"]).to(x).view(-1, 1, 1, 1)
+            bias = l["bn_shift"] if l["bn_shift"] is not None else l["bias"]
+            v = _conv64(v, wt, l["stride"], l["pad"]) + torch.from_numpy(bias).to(x)
+            if l["res"] >= 0:
+                v = v + out[l["res"]]
+            v = v.relu() if l["relu"] else v
+        elif l["op"] == "maxpool":
+            v = torch.nn.functional.max_pool2d(v.permute(0, 3, 1, 2), l["k"], l["stride"], l["pad"]).permute(0, 2, 3, 1)
+        elif l["op"] == "gap":
+            v = v.mean(dim=(1, 2))
+        else:
+            v = v.permute(0, 3, 1, 2) if l["flatten_nchw"] else v
+            v = v.reshape(v.shape[0], -1) @ torch.from_numpy(l["weight"]).to(x).t() + torch.from_numpy(l["bias"]).to(x)
+            v = v.relu() if l["relu"] else v
+        out.append(v)
+        for j in (l["src"], l.get("res", -1)):
+            if j >= 0 and last_use[j] == i:
+                out[j] = None
+    return out[-1]
+
+
+def exact(case, seed):
+    if case["kind"] == "conv":
+        x, w, bias, res = _conv_inputs(case, seed)
+        y = _conv64(x.double(), w.double(), case["stride"], case["k"] // 2) + bias.double()
+        return (y + res.double() if res is not None else y).relu()
+    imgs = _images(case, seed)
+    mean, std = (torch.tensor(v, dtype=torch.float64, device="cuda").view(1, 3, 1, 1) for v in (MEAN, STD))
+    x = torch.cat([torch.nn.functional.interpolate(im.permute(2, 0, 1)[None].double(), size=(case["out"],) * 2,
+                                                   mode="bilinear", align_corners=False) for im in imgs])
+    x = ((x / 255.0 - mean) / std).permute(0, 2, 3, 1).contiguous()
+    logits = torch.stack([torch.cat([_logits64(L, part) for part in x.split(32)]) for L in _models(case["models"])])
+    probs = logits.softmax(-1)
+    whole = None  # class numbers have no 64-bit value of their own
+    return {"probs": probs, "mean": probs.mean(0), "vote": whole, "top1": whole, "logits": logits}
