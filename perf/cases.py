@@ -29,7 +29,7 @@ from paper_2003_01538_amd import flexserve as fsv
 MEAN = (0.485, 0.456, 0.406)
 STD = (0.229, 0.224, 0.225)
 TOP_CLASS = 7        # the class that the ensemble's models agree on
-TOP_BIAS = 4.0       # ... and the bias that its logit gets
+TOP_BIAS = 5.0       # ... and the bias that its logit gets
 
 # (cin, cout, kernel, stride, height = width of the input, residual): the
 # convolution layers of ResNet-18, ResNet-50 and VGG-11 with 64 channels or
@@ -183,7 +183,8 @@ def _model(arch, index):
             l["weight"] = (torch.randn(l["cout"], l["cin"], generator=g)
                            * (math.sqrt(2.0 / l["cin"]) * (HEAD_GAIN[arch] if last else 1.0))).numpy()
             l["bias"] = (0.02 * torch.randn(l["cout"], generator=g)).numpy()
-            if last:
+            if last:  # the agreed class: its logit is the bias, whatever the features of random weights are
+                l["weight"][TOP_CLASS] *= 0.2
                 l["bias"][TOP_CLASS] += TOP_BIAS
     return L
 
