@@ -46,6 +46,7 @@
 #include "lds_dma.hpp"
 
 #include <algorithm>
+#include <numeric>
 #include <type_traits>
 
 namespace fs {
@@ -484,17 +485,21 @@ __global__ void __launch_bounds__(64 * HS_NW, 1) k_conv_hs(ConvArgs a) {
 // that pixel's row whose band the first pixel's top taps start.
 template <int BM>
 int64_t patch_px(const ConvArgs& a) {
-  const int64_t HW = (int64_t)a.H * a.W, PW = a.W + 2, HP = a.H + 2;
-  const int64_t tiles = (a.M + BM - 1) / BM;
-  int64_t need = 0;
-  for (int64_t t = 0; t < tiles; ++t) {
-    const int64_t m0 = t * BM, m1 = std::min<int64_t>(a.M, m0 + BM) - 1;
-    const int64_t R0 = (m0 / HW) * HP + (m0 % HW) / a.W;      // padded row above the first pixel
-    const int64_t b1 = m1 / HW, y1 = (m1 % HW) / a.W, x1 = (m1 % HW) % a.W;
-    const int64_t q = (b1 * HP + y1 - R0) * PW + x1 + 2 * PW + 2;  // last pixel's bottom-right tap
-    need = std::max(need, q + 1);
+  const int HW = a.H * a.W, PW = a.W + 2, HP = a.H + 2;
+  // a tile's patch depends only on where in its image the tile starts, which
+  // repeats every HW / gcd(HW, BM) tiles; the last tile may be short
+  const int tiles = (a.M + BM - 1) / BM, period = HW / std::gcd(HW, BM);
+  auto need = [&](int s, int px) {  // tile starting at pixel s of an image
+    const int e = s + px - 1, b1 = e / HW, r = e - b1 * HW, y1 = r / a.W;
+    return (int64_t)(b1 * HP + y1 - s / a.W) * PW + (r - y1 * a.W) + 2 * PW + 3;  // to the last pixel's bottom-right tap
+  };
+  int64_t most = need((int)((int64_t)(tiles - 1) * BM % HW), a.M - (tiles - 1) * BM);
+  int s = 0;
+  for (int t = 0; t < std::min(tiles - 1, period); ++t) {
+    most = std::max(most, need(s, BM));
+    s = (s + BM) % HW;
   }
-  return need;
+  return most;
 }
 int64_t hs_patch_px(const ConvArgs& a) { return patch_px<HS_BM>(a); }
 
