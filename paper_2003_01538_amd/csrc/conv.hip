@@ -330,6 +330,11 @@ static const ConvTile kTilesBF16[] = {
     {96, 128, 8, "bf16dma1_96x128_w4m1_v8", 1, 4, 1},
     {160, 128, 8, "bf16hr_160x128_w4m1_v8", 0, 4, 1, 3},
     {96, 128, 8, "bf16hr_96x128_w4m1_v8", 0, 4, 1, 3},
+    {32, 32, 8, "bf16ks_32x32_w8_v8", 0, 8, 1, 4},
+    {32, 64, 8, "bf16ks_32x64_w8_v8", 0, 8, 1, 4},
+    {64, 64, 8, "bf16ks_64x64_w8_v8", 0, 8, 1, 4},
+    {64, 128, 8, "bf16ks_64x128_w8_v8", 0, 8, 1, 4},
+    {96, 128, 8, "bf16ks_96x128_w8_v8", 0, 8, 1, 4},
 };
 static const ConvTile kTilesF32[] = {
     {64, 64, 4, "f32_64x64_v4"},
@@ -345,6 +350,7 @@ const ConvTile& conv_tile(Prec p, int t) { return p == BF16 ? kTilesBF16[t] : kT
 bool conv_tile_ok(Prec p, int t, const ConvArgs& a) {
   if (t < 0 || t >= conv_num_tiles(p)) return false;
   const ConvTile& c = conv_tile(p, t);
+  if (c.halo == 4) return p == BF16 && conv_ks_ok(a, c.bm, c.bn);
   if (c.halo == 3) return p == BF16 && conv_hr_ok(a, c.bm);
   if (c.halo == 2) return p == BF16 && conv_hs_ok(a);
   if (c.halo) return p == BF16 && conv_halo_ok(a, c.th, c.tw, c.bn);
@@ -357,19 +363,31 @@ bool conv_tile_ok(Prec p, int t, const ConvArgs& a) {
 // for the streamed-weight halo kernel).
 bool conv_tile_candidate(Prec p, int t, const ConvArgs& a) {
   if (!conv_tile_ok(p, t, a)) return false;
+  if (conv_tile(p, t).halo == 4) return conv_ks_tile(p, a) == t;
   return conv_tile(p, t).halo < 2 || conv_hs_chosen(a);
+}
+
+// The tile of the kernel for layers with few tiles, where its rule takes the layer, or -1.
+int conv_ks_tile(Prec p, const ConvArgs& a) {
+  int bm = 0, bn = 0;
+  if (p != BF16 || conv_ks_pick(a, &bm, &bn) < 0) return -1;
+  for (int t = 0; t < conv_num_tiles(p); ++t)
+    if (conv_tile(p, t).halo == 4 && conv_tile(p, t).bm == bm && conv_tile(p, t).bn == bn) return t;
+  return -1;
 }
 
 // Largest useful tile: prefer tiles that keep >= 2 workgroups per CU busy,
 // then the least padding waste, then the larger tile (more reuse per byte).
-int conv_pick_tile(Prec p, const ConvArgs& a, int num_cus) {
+int conv_pick_tile(Prec p, const ConvArgs& a, int num_cus, bool ks) {
+  const int few = ks ? conv_ks_tile(p, a) : -1;
+  if (few >= 0) return few;
   int fam = -1;
   for (int t = 0; t < conv_num_tiles(p); ++t)
-    if (conv_tile_candidate(p, t, a)) fam = std::max(fam, conv_tile_family(conv_tile(p, t)));
+    if (conv_tile(p, t).halo != 4 && conv_tile_candidate(p, t, a)) fam = std::max(fam, conv_tile_family(conv_tile(p, t)));
   int best = -1;
   double best_score = -1;
   for (int t = 0; t < conv_num_tiles(p); ++t) {
-    if (!conv_tile_candidate(p, t, a) || conv_tile_family(conv_tile(p, t)) != fam) continue;
+    if (conv_tile(p, t).halo == 4 || !conv_tile_candidate(p, t, a) || conv_tile_family(conv_tile(p, t)) != fam) continue;
     const ConvTile& c = conv_tile(p, t);
     const double tm = (a.M + c.bm - 1) / c.bm, tn = (a.Cout + c.bn - 1) / c.bn;
     const double wgs = tm * tn * a.Z;
@@ -392,6 +410,11 @@ static void launch_t(const ConvArgs& a, hipStream_t s) {
 }
 
 void launch_conv(const ConvArgs& a, Prec p, int tile, hipStream_t s, bool reduce) {
+  if (p == BF16 && conv_tile(p, tile).halo == 4) {
+    const ConvTile& c = conv_tile(p, tile);
+    launch_conv_ks(a, c.bm, c.bn, s);
+    return;
+  }
   if (p == BF16 && conv_tile(p, tile).halo == 3) {
     launch_conv_hr(a, conv_tile(p, tile).bm, s);
     return;

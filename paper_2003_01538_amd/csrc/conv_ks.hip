@@ -1,0 +1,478 @@
+// Convolution for layers with few output tiles (small batches, late layers),
+// bf16: the waves of a workgroup split the REDUCTION of one output tile.
+//
+// At a small batch the other bf16 kernels give each workgroup a whole
+// reduction: the 7x7x512 3x3 layer at one image is 12 workgroups of 72
+// K-tiles, one after the other, and takes 33 us at any batch up to 32, the
+// latency of 72 dependent fetches.  Here a workgroup owns a tile of 32 FM
+// output pixels x 32 NB channels and its KS x NB waves each run a contiguous
+// KS-th of the K-tiles, with their fp32 sums added through LDS in wave order
+// at the end.  The serial chain is KS times shorter, no partial sum leaves
+// the CU, and no second launch finishes it.
+//
+// Input: all channels of the input pixels that the tile reads are staged in
+// LDS once, by direct loads, with one barrier; the waves then run without
+// meeting until the end.  For a 3x3 filter those pixels are ONE run of the
+// flattened [B*H*W] pixel index, from the first output's top-left tap to the
+// last output's bottom-right one (a run of BM + 2W + 2 for stride 1): each
+// LDS row is one pixel's 64-channel chunk (128 bytes), there are no padding
+// rows, and a tap outside the image reads a row of zeros instead.  For
+// stride 2 the run's even pixels come first, then the odd ones, so that
+// consecutive outputs still read consecutive rows (the swizzle's condition
+// for conflict-free operand reads).  For a 1x1 filter, and for a projection
+// shortcut's input, the rows are the tile's own pixels.
+//
+// Weights: each wave streams its own K-tiles straight into registers, RING
+// K-tiles ahead, from the fragment-ordered copy (one 1 KB load per k16
+// step); where only packed rows exist (the allocation-free entry point) it
+// loads 8 rows x 128 bytes per instruction and turns them through 4 KB of LDS
+// that belong to the wave alone.  The operand values, the K order within a
+// wave and the order of the waves' sums are the same on both routes, so the
+// bits are.
+#include "common.hpp"
+#include "device.hpp"
+#include "lds_dma.hpp"
+
+#include <algorithm>
+#include <cmath>
+
+namespace fs {
+
+namespace {
+
+constexpr int KS_BLK = 1024 + 64;  // LDS bytes of one 8-channel group of a 32x32 partial block (padded: 16-byte reads of 4 groups x 4 pixels hit distinct banks)
+
+constexpr int KS_WAVES = 8; // waves of a workgroup: KS along the reduction x NB along the channels
+constexpr int KS_PASS = 2;   // 32-pixel blocks whose partial sums are in LDS at a time
+
+struct KsGeom {
+  int rows;   // LDS rows per 64-channel chunk of the main input (multiple of 8)
+  int half;   // stride 2: rows of even pixels (the odd ones follow)
+  int off2;   // LDS byte offset of the projection shortcut's rows
+  int zero;   // ... of the row of zeros
+  int wbuf;   // ... of the waves' weight buffers (4 KB each; packed-row weights only)
+  int mt, nt; // tiles along M and N
+};
+
+extern __shared__ __attribute__((aligned(1024))) char ks_smem[];
+
+template <int FM, int KS, int NB, int RING, int WPS, bool WF>
+__global__ void __launch_bounds__(64 * KS * NB, WPS) k_conv_ks(ConvArgs a, KsGeom g) {
+  static_assert(KS * NB == KS_WAVES, "waves");
+  constexpr int NW = KS_WAVES, BM = 32 * FM, BN = 32 * NB;
+  char* const sm = ks_smem;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ks = wave / NB, nb = wave - ks * NB;
+  const int lr = lane >> 3, fr = lane & 31, fq = lane >> 5;
+
+  // M tiles fastest, XCD-contiguous: an XCD's workgroups share few weights
+  const int id = xcd_remap(blockIdx.x, g.mt * g.nt * a.Z);
+  const int mt = id % g.mt, nz = id / g.mt;
+  const int z = nz / g.nt, n0 = (nz - z * g.nt) * BN, m0 = mt * BM;
+
+  const int HoWo = a.Ho * a.Wo, W = a.W, S = a.stride, pad = a.pad;
+  const float inv_howo = 1.0f / (float)HoWo, inv_wo = 1.0f / (float)a.Wo;
+  const bool k1 = a.kh == 1;
+  const int CH = a.Cin / BK;
+  const int npix = a.B * a.H * W;
+
+  const __amdgpu_buffer_rsrc_t rx =
+      rsrc(reinterpret_cast<const uint16_t*>(a.x) + z * a.x_mstride, (uint32_t)((int64_t)npix * a.Cin * 2));
+  const __amdgpu_buffer_rsrc_t rw =
+      WF ? rsrc(reinterpret_cast<const uint16_t*>(a.wf) + z * a.wf_mstride, (uint32_t)((int64_t)a.Cout * a.Kp * 2))
+         : rsrc(reinterpret_cast<const uint16_t*>(a.w) + z * a.w_mstride, (uint32_t)((int64_t)a.Cout * a.Kp * 2));
+
+  // first pixel of the run (the top-left tap of output m0; may lie before the tensor)
+  int p0;
+  {
+    const int b = m0 / HoWo, r = m0 - b * HoWo, oy = r / a.Wo, ox = r - oy * a.Wo;
+    p0 = (b * a.H + oy * S) * W + ox * S - pad * (W + 1);
+  }
+
+  // ---- input rows into LDS: instruction v fills rows 8 (v % nrb) .. +8 of chunk v / nrb
+  {
+    const int nrb = g.rows >> 3, total = nrb * CH;
+    int rb = wave, cc = 0;
+    for (int v = wave; v < total; v += NW, rb += NW) {
+      while (rb >= nrb) {
+        rb -= nrb;
+        ++cc;
+      }
+      const int r = rb * 8 + lr;
+      int p;
+      if (k1) {
+        const int m = m0 + r;
+        const int b = fdiv_small(m, inv_howo), q = m - b * HoWo, oy = fdiv_small(q, inv_wo), ox = q - oy * a.Wo;
+        p = m < a.M ? (b * a.H + oy * S) * W + ox * S : -1;
+      } else {
+        p = p0 + (S == 1 ? r : (r < g.half ? 2 * r : 2 * (r - g.half) + 1));
+      }
+      const int lc = (lane & 7) ^ swz(r);
+      const uint32_t off =
+          (unsigned)p < (unsigned)npix ? (uint32_t)(((int64_t)p * a.Cin + cc * BK + lc * 8) * 2) : OOB;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(sm + v * 1024), 16, off, 0, 0, 0);
+    }
+  }
+  const int CH2 = a.x2 ? a.Cin2 / BK : 0;
+  if (CH2) {  // the projection shortcut's input: the tile's own pixels
+    const __amdgpu_buffer_rsrc_t rx2 = rsrc(reinterpret_cast<const uint16_t*>(a.x2) + z * a.x2_mstride,
+                                            (uint32_t)((int64_t)a.B * a.H2 * a.W2 * a.Cin2 * 2));
+    for (int v = wave; v < CH2 * (BM / 8); v += NW) {
+      const int cc = v / (BM / 8), r = (v - cc * (BM / 8)) * 8 + lr, m = m0 + r;
+      const int b = fdiv_small(m, inv_howo), q = m - b * HoWo, oy = fdiv_small(q, inv_wo), ox = q - oy * a.Wo;
+      const int lc = (lane & 7) ^ swz(r);
+      const uint32_t off =
+          m < a.M ? (uint32_t)(((((int64_t)b * a.H2 + oy * a.stride2) * a.W2 + ox * a.stride2) * a.Cin2 + cc * BK + lc * 8) * 2)
+                  : OOB;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx2, (lds_void*)(sm + g.off2 + v * 1024), 16, off, 0, 0, 0);
+    }
+  }
+  if (!k1 && tid < 8) *reinterpret_cast<uint4*>(sm + g.zero + tid * 16) = uint4{0, 0, 0, 0};
+
+  // ---- this wave's K-tiles and its weights
+  const int nk1 = a.kh * a.kw * CH, nk = nk1 + CH2;
+  const int u0 = ks * nk / KS, u1 = (ks + 1) * nk / KS;
+  const int nw = n0 + nb * 32;
+  const uint32_t wbase = WF ? (uint32_t)((int64_t)(nw / 32) * (a.Kp / 16) * 1024 + lane * 16)
+                            : (uint32_t)(((int64_t)(nw + lr) * a.Kp + (lane & 7) * 8) * 2);
+  const uint32_t wrow8 = (uint32_t)a.Kp * 16;  // bytes of 8 packed rows
+  auto load_w = [&](int u, uint4 (&v)[4]) {
+    // past this wave's range: out of range, so that every step issues the same loads
+    const uint32_t b = u < u1 ? wbase + (uint32_t)u * (WF ? 4096u : 128u) : OOB;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      v[s] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rw, b + (WF ? 1024u * s : wrow8 * s), 0, 0));
+  };
+
+  // ---- this lane's pixels: run position of the centre tap, top-left input coordinates
+  int q0[FM], iy0[FM], ix0[FM];
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    const int m = m0 + i * 32 + fr;
+    const int b = fdiv_small(m, inv_howo), r = m - b * HoWo, oy = fdiv_small(r, inv_wo), ox = r - oy * a.Wo;
+    // past M: never inside the image (a 1x1 filter's rows past M hold zeros themselves)
+    iy0[i] = m < a.M || k1 ? oy * S - pad : -(1 << 28);
+    ix0[i] = ox * S - pad;
+    q0[i] = k1 ? i * 32 + fr : (b * a.H + oy * S) * W + ox * S - pad * (W + 1) - p0;
+  }
+  const int sh = k1 ? 0 : S - 1;  // stride 2: row = j / 2, + half for odd j
+
+  floatx16 acc[FM];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+
+  // position of a K-tile: filter row and column, 64-channel chunk (scalars,
+  // advanced one K-tile at a time; past the filter: the shortcut's chunk)
+  int ky, kx, cc;
+  {
+    const int tap = u0 / CH;
+    cc = u0 - tap * CH;
+    ky = tap / a.kw;
+    kx = tap - ky * a.kw;
+    if (u0 >= nk1) cc = u0 - nk1;
+  }
+  // LDS address of this lane's first operand (k16 step 0) of block i; step s
+  // is at address ^ (s << 5), since rows are 128 bytes and chunks are swizzled by XOR
+  int ad[FM];
+  auto address = [&](int u) {
+    if (u < nk1) {  // wave-uniform
+      const int cbase = cc * g.rows * ROW, dq = k1 ? 0 : ky * W + kx;
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        const int j = q0[i] + dq, row = (j >> sh) + (j & sh) * g.half;
+        const bool ok = (unsigned)(iy0[i] + ky) < (unsigned)a.H && (unsigned)(ix0[i] + kx) < (unsigned)W;
+        const int keep = 0 - (int)ok;  // a bitwise blend: the compiler branched around a select
+        ad[i] = (((cbase + row * ROW) & keep) | (g.zero & ~keep)) + ((fq ^ swz(row)) << 4);
+      }
+    } else {
+      const int cbase = g.off2 + cc * BM * ROW;
+#pragma unroll
+      for (int i = 0; i < FM; ++i) ad[i] = cbase + (i * 32 + fr) * ROW + ((fq ^ swz(i * 32 + fr)) << 4);
+    }
+  };
+  auto advance = [&](int u) {  // to K-tile u
+    if (++cc == CH && u <= nk1) {
+      cc = 0;
+      if (++kx == a.kw) {
+        kx = 0;
+        ++ky;
+      }
+    }
+  };
+  auto read_half = [&](int h, bf16x8 (&f)[2][FM]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < FM; ++i) f[s][i] = *reinterpret_cast<const bf16x8*>(sm + (ad[i] ^ ((2 * h + s) << 5)));
+  };
+  auto mma_half = [&](const bf16x8 (&f)[2][FM], const bf16x8& b0, const bf16x8& b1) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b0, f[0][i], acc[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b1, f[1][i], acc[i], 0, 0, 0);
+  };
+
+  uint4 wr[RING][4];
+#pragma unroll
+  for (int d = 0; d < RING; ++d) load_w(u0 + d, wr[d]);
+  wait_vmcnt<4 * RING>();  // the input rows landed; the weights may be in flight
+  wait_lgkm0();            // ...and the zeros
+  wg_barrier();
+  // Each half K-tile's operands are read while the other half's MFMAs run
+  // (reading them where they are used left a wave waiting for LDS four times
+  // per K-tile, with one other wave on its SIMD to fill in).
+  bf16x8 fa[2][FM], fb[2][FM];
+  address(u0);
+  read_half(0, fa);
+  auto k_tile = [&](int u, const uint4 (&wv)[4]) {
+    bf16x8 bw[4];
+    if constexpr (WF) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) bw[s] = __builtin_bit_cast(bf16x8, wv[s]);
+    } else {  // rows of 8 x 128 bytes -> fragments, through this wave's own LDS (in order within the wave)
+      char* const wb = sm + g.wbuf + wave * 4096;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int r = s * 8 + lr;
+        *reinterpret_cast<uint4*>(wb + r * ROW + (((lane & 7) ^ swz(r)) << 4)) = wv[s];
+      }
+      __asm__ __volatile__("" ::: "memory");
+#pragma unroll
+      for (int s = 0; s < 4; ++s)  // after the writes above: one wave's LDS operations run in order
+        bw[s] = *reinterpret_cast<const bf16x8*>(wb + fr * ROW + (((2 * s + fq) ^ swz(fr)) << 4));
+    }
+    read_half(1, fb);
+    __builtin_amdgcn_sched_barrier(0);
+    mma_half(fa, bw[0], bw[1]);
+    if (u + 1 < u1) {
+      advance(u + 1);
+      address(u + 1);
+    }
+    read_half(0, fa);  // the next K-tile's (after the last one: read again, unused)
+    __builtin_amdgcn_sched_barrier(0);
+    mma_half(fb, bw[2], bw[3]);
+  };
+  // whole rings first: no path skips a load in the loop, so that the
+  // compiler's waits leave the younger ones in flight
+  int u = u0;
+  for (; u + RING <= u1; u += RING) {
+#pragma unroll
+    for (int d = 0; d < RING; ++d) {
+      k_tile(u + d, wr[d]);
+      load_w(u + d + RING, wr[d]);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < RING - 1; ++d)
+    if (u + d < u1) k_tile(u + d, wr[d]);
+
+  // ---- the waves' sums through LDS, KS_PASS 32-pixel blocks at a time.
+  // D[n][m]: lane l holds pixel l % 32 and channels 8 g + 4 (l / 32) + r, one
+  // 16-byte piece per (block, g).  Then one item = one pixel x 8 channels:
+  // the KS sums in order, bias, residual, ReLU, one 16-byte store (4 NB items
+  // make a pixel's 64 NB bytes)
+  const float* __restrict__ bias = a.bias + z * a.b_mstride;
+  const uint32_t obytes = (uint32_t)((int64_t)a.M * a.Cout * 2);
+  const bool has_res = a.res != nullptr;
+  const __amdgpu_buffer_rsrc_t rres =
+      has_res ? rsrc(reinterpret_cast<const uint16_t*>(a.res) + z * a.res_mstride, obytes) : rsrc(a.y, 0u);
+  const __amdgpu_buffer_rsrc_t ry = rsrc(reinterpret_cast<uint16_t*>(a.y) + z * a.y_mstride, obytes);
+  constexpr int PB = FM < KS_PASS ? FM : KS_PASS;  // blocks per pass
+  constexpr int WAVE = PB * 4 * KS_BLK;            // LDS bytes per wave
+#pragma unroll
+  for (int i0 = 0; i0 < FM; i0 += PB) {
+    wait_lgkm0();
+    wg_barrier();  // every wave has read its last operands, or the last pass's sums
+#pragma unroll
+    for (int i = i0; i < FM && i < i0 + PB; ++i)
+#pragma unroll
+      for (int gg = 0; gg < 4; ++gg)
+        *reinterpret_cast<float4*>(sm + wave * WAVE + ((i - i0) * 4 + gg) * KS_BLK + lane * 16) =
+            make_float4(acc[i][gg * 4], acc[i][gg * 4 + 1], acc[i][gg * 4 + 2], acc[i][gg * 4 + 3]);
+    wait_lgkm0();
+    wg_barrier();
+    for (int it = tid; it < (FM - i0 < PB ? FM - i0 : PB) * 32 * 4 * NB; it += 64 * NW) {
+      const int c8 = it % (4 * NB), px = it / (4 * NB), m = m0 + i0 * 32 + px, n = n0 + c8 * 8;
+      if (m >= a.M) continue;
+      const uint32_t o = (uint32_t)(((int64_t)m * a.Cout + n) * 2);
+      const uint4 rv = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rres, o, 0, 0));  // zeros without one
+      const float4 b0 = *reinterpret_cast<const float4*>(bias + n), b1 = *reinterpret_cast<const float4*>(bias + n + 4);
+      const char* src = sm + (c8 >> 2) * WAVE + ((px >> 5) * 4 + (c8 & 3)) * KS_BLK + (px & 31) * 16;
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const char* s = src + k * NB * WAVE;
+        const float4 lo = *reinterpret_cast<const float4*>(s), hi = *reinterpret_cast<const float4*>(s + 512);
+        if (k == 0) {
+          v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
+          v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
+        } else {
+          v[0] += lo.x; v[1] += lo.y; v[2] += lo.z; v[3] += lo.w;
+          v[4] += hi.x; v[5] += hi.y; v[6] += hi.z; v[7] += hi.w;
+        }
+      }
+      v[0] += b0.x; v[1] += b0.y; v[2] += b0.z; v[3] += b0.w;
+      v[4] += b1.x; v[5] += b1.y; v[6] += b1.z; v[7] += b1.w;
+      if (has_res) {
+        float rr[8];
+        bf8_to_f8(rv, rr);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += rr[e];
+      }
+      if (a.relu)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, f8_to_bf8(v)), ry, o, 0, 0);
+    }
+  }
+}
+
+// LDS plan of a layer for tiles of bm pixels; *lds = bytes needed.  packed:
+// with the buffers that turn packed weight rows.
+KsGeom ks_geom(const ConvArgs& a, int bm, int bn, bool packed, size_t* lds) {
+  KsGeom g{};
+  g.mt = (a.M + bm - 1) / bm;
+  g.nt = a.Cout / bn;
+  int64_t need = bm;  // a 1x1 filter reads the tile's own pixels
+  if (a.kh == 3) {
+    // an upper bound over every tile: a step to the next output moves `stride`
+    // pixels, the end of an output row stride (W - Wo) more, the end of an
+    // image (H - stride Ho) W more (never positive for stride 2)
+    const int64_t steps = bm - 1, rows = (steps + a.Wo - 1) / a.Wo, imgs = (steps + a.Ho * a.Wo - 1) / (a.Ho * a.Wo);
+    need = a.stride * steps + rows * a.stride * (a.W - a.Wo) +
+           imgs * std::max(0, a.H - a.stride * a.Ho) * (int64_t)a.W + 2 * (a.W + 1) + 1;
+  }
+  g.half = a.stride == 2 ? (int)((need + 1) / 2) : 0;
+  const int64_t nr = a.stride == 2 && a.kh == 3 ? 2 * (int64_t)g.half : need;
+  g.rows = (int)((nr + 7) / 8 * 8);
+  const int64_t CH = a.Cin / BK, CH2 = a.x2 ? a.Cin2 / BK : 0;
+  int64_t off = CH * g.rows * ROW;
+  g.off2 = (int)std::min<int64_t>(off, INT32_MAX);
+  off += CH2 * bm * ROW;
+  g.zero = (int)std::min<int64_t>(off, INT32_MAX);
+  if (a.kh == 3) off += ROW;
+  if (packed) {
+    off = (off + 1023) / 1024 * 1024;
+    g.wbuf = (int)std::min<int64_t>(off, INT32_MAX);
+    off += (int64_t)KS_WAVES * 4096;
+  }
+  *lds = (size_t)std::max<int64_t>(off, (int64_t)KS_WAVES * std::min(bm / 32, KS_PASS) * 4 * KS_BLK);
+  return g;
+}
+
+}  // namespace
+
+// Layers the kernel can run: 3x3 (pad 1) or 1x1 (pad 0) filters of stride 1
+// or 2 on whole 64-channel chunks, whole channel blocks, and the tile's
+// input in LDS.
+bool conv_ks_ok(const ConvArgs& a, int bm, int bn) {
+  if (a.kh != a.kw || !((a.kh == 3 && a.pad == 1) || (a.kh == 1 && a.pad == 0)) || a.stride < 1 || a.stride > 2)
+    return false;
+  if (a.Cin % BK || a.Cout % bn || (a.x2 && !a.wf)) return false;
+  const int K1 = a.kh * a.kw * a.Cin;
+  if (a.x2 ? (a.Cin2 % BK || a.K1 != K1 || a.K != K1 + a.Cin2 || (a.Ho - 1) * a.stride2 >= a.H2 ||
+              (a.Wo - 1) * a.stride2 >= a.W2 || (int64_t)a.B * a.H2 * a.W2 * a.Cin2 * 2 >= (1ll << 31))
+           : a.K != K1)
+    return false;
+  if (a.K != a.Kp || (a.Ho - 1) * a.stride - a.pad >= a.H || (a.Wo - 1) * a.stride - a.pad >= a.W) return false;
+  if ((int64_t)a.M * a.Cout * 2 >= (1ll << 31)) return false;
+  if ((int64_t)a.M + 4096 >= (1 << 22) || a.K / BK >= (1 << 22)) return false;  // fdiv_small range
+  if ((int64_t)a.B * a.H * a.W * a.Cin * 2 >= (1ll << 31) || (int64_t)a.Cout * a.Kp * 2 >= (1ll << 31)) return false;
+  if (a.K / BK < KS_WAVES / (bn / 32)) return false;  // every wave has a K-tile
+  size_t lds = 0;
+  ks_geom(a, bm, bn, !a.x2, &lds);  // whichever weights there are: the choice of kernel does not depend on them
+  return lds <= 160 * 1024;
+}
+
+void launch_conv_ks(const ConvArgs& a_in, int bm, int bn, hipStream_t s) {
+  ConvArgs a = a_in;  // outputs are always finished here
+  a.split = 1;
+  a.partial = nullptr;
+  size_t lds = 0;
+  const KsGeom g = ks_geom(a, bm, bn, !a.wf, &lds);
+  const dim3 grid((unsigned)(g.mt * g.nt * a.Z)), block(64 * KS_WAVES);
+#define FS_KS(FMv, KSv, NBv, RINGv, WPSv)                                                              \
+  if (bm == 32 * FMv && bn == 32 * NBv) {                                                              \
+    if (a.wf)                                                                                          \
+      hipLaunchKernelGGL((k_conv_ks<FMv, KSv, NBv, RINGv, WPSv, true>), grid, block, lds, s, a, g);    \
+    else  /* the turned weights take registers: a shorter ring */                                      \
+      hipLaunchKernelGGL((k_conv_ks<FMv, KSv, NBv, 2, WPSv, false>), grid, block, lds, s, a, g);       \
+    return;                                                                                            \
+  }
+  FS_KS(1, 8, 1, 4, 4) FS_KS(1, 4, 2, 4, 4) FS_KS(2, 4, 2, 2, 4) FS_KS(2, 2, 4, 2, 4) FS_KS(3, 2, 4, 3, 2)
+#undef FS_KS
+}
+
+// The tiles of the rule below: pixels, channels, waves along the reduction,
+// the measured time of one K-tile of a wave (us), and whether its registers
+// let two workgroups share a CU.
+struct KsTile {
+  int bm, bn, ks;
+  double us;
+  int two;
+};
+static const KsTile kKsTiles[] = {
+    {32, 32, 8, 0.27, 1}, {32, 64, 4, 0.25, 1}, {64, 64, 4, 0.37, 1}, {64, 128, 2, 0.36, 1}, {96, 128, 2, 0.62, 0}};
+
+// Estimated time (us) of the layer on this kernel: a launch, then rounds of
+// workgroups, each its share of the K-tiles plus the staging of its input.
+static double ks_estimate(const ConvArgs& a, const KsTile& t, double cus) {
+  size_t lds = 0;
+  const KsGeom g = ks_geom(a, t.bm, t.bn, false, &lds);
+  const double r = (double)g.mt * g.nt * a.Z / cus;
+  const int nk = a.K / BK, per_cu = std::min(t.two ? 2 : 1, (int)(160 * 1024 / lds));
+  const double wg = (nk + t.ks - 1) / t.ks * t.us + 0.9 + (double)lds / (80 * 1024);
+  if (r > 3) return 1e30;  // outside what was measured
+  return 3.6 + wg * (r <= 1 ? 1.0 : per_cu == 1 ? std::ceil(r) : std::max(1.5, 1.1 * r));
+}
+
+// The same for the kernel that would run the layer otherwise.
+static double other_estimate(const ConvArgs& a, double cus) {
+  const int nk = a.K / BK;
+  const double t96 = (double)((a.M + 95) / 96) * ((a.Cout + 127) / 128) * a.Z;  // 96 x 128 tiles
+  if (conv_hs_chosen(a)) return 4.0 + nk * 0.37 * std::max(1.0, t96 / cus);
+  if (conv_halo_ok(a, 4, 56, 64))
+    return 4.6 + 4.1 * std::ceil((double)a.B * ((a.Ho + 3) / 4) * (a.Cout / 64) * a.Z / cus);
+  const int split = conv_split(BF16, a, (int)cus);
+  const double t = t96 * split, k = (double)nk / split;
+  double us = 4.5 + (t >= cus ? (k * 0.42 + 1.0) * t / cus : k * 0.25 + 1.0);
+  if (split > 1) us += 3.0 + (double)split * a.M * a.Cout * a.Z * 8 / 6.5e6;  // the completion: partial sums out and in
+  return us;
+}
+
+// Which of this kernel's tiles runs the layer, or -1.  The estimates above
+// were fitted to back-to-back launches of every tile on ten layer shapes of
+// ResNet-18 and ResNet-50 at 1 to 64 images and one or three models (100
+// cases).  The rule picks within 6 % of the fastest kernel in 94 of them and
+// within 21 % in all.  Measured (us, this kernel against the one that ran
+// before): 7x7x512 3x3, three models, B = 1 / 8 / 16: 7.3 / 12.4 / 17.6
+// against 26.3 / 32.4 / 32.5; 14x14x256 B = 1 / 8: 6.1 / 11.3 against 15.9 /
+// 16.6; 28x28x128 to 256 stride 2 (split over workgroups before), B = 8 / 16:
+// 9.3 / 12.7 against 16.9 / 22.5.  With more tiles the other kernels win:
+// 14x14x256 B = 32 24.6 against 26.4, 28x28x128 to 256 stride 2 17.3 against
+// 24.0.  It depends on the shape and the batch only (256 CUs, the chip's),
+// never on timing, so a result's bits do not vary from run to run.
+int conv_ks_pick(const ConvArgs& a_in, int* bm, int* bn) {
+  constexpr double cus = 256;
+  ConvArgs a = a_in;
+  a.split = 1;  // the caller's split is the implicit GEMM's
+  double best = 1e30;
+  int pick = -1;
+  for (int i = 0; i < (int)(sizeof(kKsTiles) / sizeof(KsTile)); ++i) {
+    if (!conv_ks_ok(a, kKsTiles[i].bm, kKsTiles[i].bn)) continue;
+    const double e = ks_estimate(a, kKsTiles[i], cus);
+    if (e < best) {
+      best = e;
+      pick = i;
+    }
+  }
+  if (pick < 0 || best >= 0.97 * other_estimate(a, cus)) return -1;
+  *bm = kKsTiles[pick].bm;
+  *bn = kKsTiles[pick].bn;
+  return pick;
+}
+
+}  // namespace fs

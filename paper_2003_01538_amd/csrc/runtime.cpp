@@ -973,10 +973,18 @@ const std::vector<std::vector<int>>& tiles_for(fs_ensemble* e, int B, hipStream_
         e->workspace_bytes += (int64_t)e->conv_partial.bytes;
         a.partial = static_cast<float*>(e->conv_partial.p);
       }
+      // a layer of few tiles runs with its reduction split over a workgroup's
+      // waves, in the tile its rule names: nothing to time (FS_TUNE=1, which
+      // times every layer, times that one tile)
+      const int ruled = conv_pick_tile(e->prec, a, e->num_cus);
+      if (e->tune != 1 && ruled >= 0 && conv_tile_family(conv_tile(e->prec, ruled)) == 4) {
+        choice[gi][li] = ruled;
+        continue;
+      }
       int fam = -1;  // the layer runs in the highest kernel family among its candidates
       for (int t = 0; t < conv_num_tiles(e->prec); ++t)
         if (conv_tile_candidate(e->prec, t, a)) fam = std::max(fam, conv_tile_family(conv_tile(e->prec, t)));
-      int best = conv_pick_tile(e->prec, a, e->num_cus);
+      int best = ruled;
       const int from_table = e->tune == 1 ? -1 : table_tile(e, a, bucket, fam);
       if (from_table >= 0) best = from_table;
       if (e->tune == 1 || e->tune == 3 || (e->tune == 2 && from_table < 0)) {
@@ -1112,7 +1120,9 @@ void run_pass(fs_ensemble* e, const uint8_t* d_pixels, const ImageDesc* d_desc, 
       switch (P.op) {
         case FS_OP_CONV: {
           if (P.proj_into >= 0) break;  // runs inside its block's last conv
-          const ConvArgs a = conv_args(e, g, P, B, y, y_ms);
+          ConvArgs a = conv_args(e, g, P, B, y, y_ms);
+          // only the implicit GEMM splits K over workgroups
+          if (P.pool_fused || !conv_tile_direct(conv_tile(p, tiles[gi][li]))) a.split = 1;
           if (conv_partial_floats(a) * 4 > (g.conv_partial.p ? g.conv_partial.bytes : e->conv_partial.bytes))
             fail(FS_ERR_INTERNAL, "split-K scratch too small for this batch size");
           const int tile = tiles[gi][li];
@@ -1221,9 +1231,9 @@ int launches_per_pass(fs_ensemble* e) {
         n += fc_launches(fc_pick_split(e->prec, e->max_batch, P.K, P.out.C, g.Z, e->num_cus));
       } else if (P.op == FS_OP_CONV && P.proj_into < 0) {
         const ConvArgs a = conv_args(e, g, P, e->max_batch, nullptr, 0);
-        n += (!P.pool_fused && a.split > 1) ? 2 : 1;
         const int gi = (int)(&g - e->groups.data());
-        const int tile = tl ? (*tl)[gi][li] : conv_pick_tile(e->prec, a, e->num_cus);
+        const int tile = tl ? (*tl)[gi][li] : P.pool_fused ? -1 : conv_pick_tile(e->prec, a, e->num_cus);
+        n += (!P.pool_fused && a.split > 1 && tile >= 0 && conv_tile_direct(conv_tile(e->prec, tile))) ? 2 : 1;
         if (P.gap_only && e->prec == BF16 && tile >= 0 && conv_tile_direct(conv_tile(e->prec, tile)) &&
             conv_reduce_gap_ok(a))
           skip_next = true;
@@ -1518,9 +1528,13 @@ fs_status fs_conv_bf16_device_noalloc(const void* d_in, int32_t B, int32_t H, in
     a.kh = kh; a.kw = kw; a.stride = stride; a.pad = pad; a.relu = relu ? 1 : 0;
     a.K = kh * kw * Cin; a.Kp = a.K; a.M = B * Ho * Wo; a.Z = 1;
     const int cus = num_cus_of(dev);
-    const int tl = conv_pick_tile(BF16, a, cus);
-    if (tl < 0 || !conv_tile_ok(BF16, tl, a)) fail(FS_ERR_UNSUPPORTED, "no conv kernel takes this shape");
-    if (conv_tile_direct(conv_tile(BF16, tl))) {
+    // a shape whose reduction the implicit GEMM splits over workgroups is
+    // taken only if its partial sums fit the scratch array, whichever kernel
+    // then runs it: what the entry point accepts does not follow the kernels
+    const int tg = conv_pick_tile(BF16, a, cus, false);
+    if (tg < 0 || !conv_tile_ok(BF16, tg, a)) fail(FS_ERR_UNSUPPORTED, "no conv kernel takes this shape");
+    int tl = tg;
+    if (conv_tile_direct(conv_tile(BF16, tg))) {
       a.split = conv_split(BF16, a, cus);
       if (a.split > 1) {
         if (conv_partial_floats(a) > kNoallocScratchFloats)
@@ -1530,6 +1544,8 @@ fs_status fs_conv_bf16_device_noalloc(const void* d_in, int32_t B, int32_t H, in
         a.partial = noalloc_scratch(dev);
       }
     }
+    const int few = conv_ks_tile(BF16, a);
+    if (few >= 0) tl = few;
     launch_conv(a, BF16, tl, static_cast<hipStream_t>(stream));
     HIPCHK(hipGetLastError());
   });

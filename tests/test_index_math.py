@@ -48,3 +48,27 @@ def test_the_half_offset_is_needed():
         n = boundary_dividends(d)
         bad += int(np.count_nonzero(fdiv(n, d, half=0.0) != n // d))
     assert bad > 0
+
+
+def test_the_run_of_input_pixels_of_a_tile_is_bounded():
+    """The kernel that stages all input pixels of a tile as one run of the
+    flattened pixel index sizes it in closed form: stride (bm - 1), plus
+    stride (W - Wo) per output row's end, (H - stride Ho) W per image's end
+    where that is positive, plus the taps around it.  No tile of any layer
+    is longer."""
+    rng = np.random.default_rng(4)
+    for _ in range(400):
+        B, H, W = int(rng.integers(1, 6)), int(rng.integers(1, 31)), int(rng.integers(1, 31))
+        for s in (1, 2):
+            Ho, Wo = (H - 1) // s + 1, (W - 1) // s + 1
+            m = np.arange(B * Ho * Wo)
+            b, r = m // (Ho * Wo), m % (Ho * Wo)
+            centre = (b * H + r // Wo * s) * W + r % Wo * s
+            assert np.all(np.diff(centre) > 0)
+            for bm in (32, 64, 96):
+                steps = bm - 1
+                need = (s * steps + -(-steps // Wo) * s * (W - Wo) + -(-steps // (Ho * Wo)) * max(0, H - s * Ho) * W
+                        + 2 * (W + 1) + 1)
+                first = np.arange(0, m.size, bm)
+                last = np.minimum(first + bm, m.size) - 1
+                assert np.max(centre[last] - centre[first]) + 2 * (W + 1) + 1 <= need, (B, H, W, s, bm)
