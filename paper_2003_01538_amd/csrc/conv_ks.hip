@@ -26,9 +26,9 @@
 // K-tiles ahead, from the fragment-ordered copy (one 1 KB load per k16
 // step); where only packed rows exist (the allocation-free entry point) it
 // loads 8 rows x 128 bytes per instruction and turns them through 4 KB of LDS
-// that belong to the wave alone.  The operand values, the K order within a
-// wave and the order of the waves' sums are the same on both routes, so the
-// bits are.
+// that belong to the wave alone, or reads 32 rows as they lie where there is
+// no LDS left.  The operand values, the K order within a wave and the order of
+// the waves' sums are the same on every route, so the bits are.
 #include "common.hpp"
 #include "device.hpp"
 #include "lds_dma.hpp"
@@ -56,7 +56,12 @@ struct KsGeom {
 
 extern __shared__ __attribute__((aligned(1024))) char ks_smem[];
 
-template <int FM, int KS, int NB, int RING, int WPS, bool WF>
+// WT: where the weights come from: the fragment-ordered copy, packed rows turned
+// through LDS, or packed rows read as they lie (32 rows per load, slower, where
+// the input leaves no LDS to turn them).
+enum { W_FRAG, W_TURN, W_ROWS };
+
+template <int FM, int KS, int NB, int RING, int WPS, int WT>
 __global__ void __launch_bounds__(64 * KS * NB, WPS) k_conv_ks(ConvArgs a, KsGeom g) {
   static_assert(KS * NB == KS_WAVES, "waves");
   constexpr int NW = KS_WAVES, BM = 32 * FM, BN = 32 * NB;
@@ -80,7 +85,7 @@ __global__ void __launch_bounds__(64 * KS * NB, WPS) k_conv_ks(ConvArgs a, KsGeo
   const __amdgpu_buffer_rsrc_t rx =
       rsrc(reinterpret_cast<const uint16_t*>(a.x) + z * a.x_mstride, (uint32_t)((int64_t)npix * a.Cin * 2));
   const __amdgpu_buffer_rsrc_t rw =
-      WF ? rsrc(reinterpret_cast<const uint16_t*>(a.wf) + z * a.wf_mstride, (uint32_t)((int64_t)a.Cout * a.Kp * 2))
+      WT == W_FRAG ? rsrc(reinterpret_cast<const uint16_t*>(a.wf) + z * a.wf_mstride, (uint32_t)((int64_t)a.Cout * a.Kp * 2))
          : rsrc(reinterpret_cast<const uint16_t*>(a.w) + z * a.w_mstride, (uint32_t)((int64_t)a.Cout * a.Kp * 2));
 
   // first pixel of the run (the top-left tap of output m0; may lie before the tensor)
@@ -134,15 +139,16 @@ __global__ void __launch_bounds__(64 * KS * NB, WPS) k_conv_ks(ConvArgs a, KsGeo
   const int nk1 = a.kh * a.kw * CH, nk = nk1 + CH2;
   const int u0 = ks * nk / KS, u1 = (ks + 1) * nk / KS;
   const int nw = n0 + nb * 32;
-  const uint32_t wbase = WF ? (uint32_t)((int64_t)(nw / 32) * (a.Kp / 16) * 1024 + lane * 16)
-                            : (uint32_t)(((int64_t)(nw + lr) * a.Kp + (lane & 7) * 8) * 2);
-  const uint32_t wrow8 = (uint32_t)a.Kp * 16;  // bytes of 8 packed rows
+  const uint32_t wbase = WT == W_FRAG   ? (uint32_t)((int64_t)(nw / 32) * (a.Kp / 16) * 1024 + lane * 16)
+                         : WT == W_TURN ? (uint32_t)(((int64_t)(nw + lr) * a.Kp + (lane & 7) * 8) * 2)
+                                        : (uint32_t)(((int64_t)(nw + fr) * a.Kp + fq * 8) * 2);
+  const uint32_t wstep = WT == W_FRAG ? 1024u : WT == W_TURN ? (uint32_t)a.Kp * 16 : 32u;  // load to load: k16 steps, or 8 packed rows
   auto load_w = [&](int u, uint4 (&v)[4]) {
     // past this wave's range: out of range, so that every step issues the same loads
-    const uint32_t b = u < u1 ? wbase + (uint32_t)u * (WF ? 4096u : 128u) : OOB;
+    const uint32_t b = u < u1 ? wbase + (uint32_t)u * (WT == W_FRAG ? 4096u : 128u) : OOB;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
-      v[s] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rw, b + (WF ? 1024u * s : wrow8 * s), 0, 0));
+      v[s] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rw, b + wstep * s, 0, 0));
   };
 
   // ---- this lane's pixels: run position of the centre tap, top-left input coordinates
@@ -229,7 +235,7 @@ __global__ void __launch_bounds__(64 * KS * NB, WPS) k_conv_ks(ConvArgs a, KsGeo
   read_half(0, fa);
   auto k_tile = [&](int u, const uint4 (&wv)[4]) {
     bf16x8 bw[4];
-    if constexpr (WF) {
+    if constexpr (WT != W_TURN) {
 #pragma unroll
       for (int s = 0; s < 4; ++s) bw[s] = __builtin_bit_cast(bf16x8, wv[s]);
     } else {  // rows of 8 x 128 bytes -> fragments, through this wave's own LDS (in order within the wave)
@@ -383,7 +389,7 @@ bool conv_ks_ok(const ConvArgs& a, int bm, int bn) {
   if ((int64_t)a.B * a.H * a.W * a.Cin * 2 >= (1ll << 31) || (int64_t)a.Cout * a.Kp * 2 >= (1ll << 31)) return false;
   if (a.K / BK < KS_WAVES / (bn / 32)) return false;  // every wave has a K-tile
   size_t lds = 0;
-  ks_geom(a, bm, bn, !a.x2, &lds);  // whichever weights there are: the choice of kernel does not depend on them
+  ks_geom(a, bm, bn, false, &lds);  // the choice of kernel does not depend on the form of the weights
   return lds <= 160 * 1024;
 }
 
@@ -392,15 +398,20 @@ void launch_conv_ks(const ConvArgs& a_in, int bm, int bn, hipStream_t s) {
   a.split = 1;
   a.partial = nullptr;
   size_t lds = 0;
-  const KsGeom g = ks_geom(a, bm, bn, !a.wf, &lds);
+  KsGeom g = ks_geom(a, bm, bn, !a.wf, &lds);
+  const bool rows = lds > 160 * 1024;  // no room to turn packed rows
+  if (rows) g = ks_geom(a, bm, bn, false, &lds);
   const dim3 grid((unsigned)(g.mt * g.nt * a.Z)), block(64 * KS_WAVES);
-#define FS_KS(FMv, KSv, NBv, RINGv, WPSv)                                                              \
-  if (bm == 32 * FMv && bn == 32 * NBv) {                                                              \
-    if (a.wf)                                                                                          \
-      hipLaunchKernelGGL((k_conv_ks<FMv, KSv, NBv, RINGv, WPSv, true>), grid, block, lds, s, a, g);    \
-    else  /* the turned weights take registers: a shorter ring */                                      \
-      hipLaunchKernelGGL((k_conv_ks<FMv, KSv, NBv, 2, WPSv, false>), grid, block, lds, s, a, g);       \
-    return;                                                                                            \
+  // the turned weights take registers: a shorter ring
+#define FS_KS(FMv, KSv, NBv, RINGv, WPSv)                                                               \
+  if (bm == 32 * FMv && bn == 32 * NBv) {                                                               \
+    if (a.wf)                                                                                           \
+      hipLaunchKernelGGL((k_conv_ks<FMv, KSv, NBv, RINGv, WPSv, W_FRAG>), grid, block, lds, s, a, g);   \
+    else if (rows)                                                                                      \
+      hipLaunchKernelGGL((k_conv_ks<FMv, KSv, NBv, RINGv, WPSv, W_ROWS>), grid, block, lds, s, a, g);   \
+    else                                                                                                \
+      hipLaunchKernelGGL((k_conv_ks<FMv, KSv, NBv, 2, WPSv, W_TURN>), grid, block, lds, s, a, g);       \
+    return;                                                                                             \
   }
   FS_KS(1, 8, 1, 4, 4) FS_KS(1, 4, 2, 4, 4) FS_KS(2, 4, 2, 2, 4) FS_KS(2, 2, 4, 2, 4) FS_KS(3, 2, 4, 3, 2)
 #undef FS_KS

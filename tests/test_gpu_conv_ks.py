@@ -58,7 +58,8 @@ def test_every_tile_matches_the_oracle_and_the_general_kernels(gpu_lib, ci):
 @pytest.mark.parametrize("case", [(1, 7, 7, 512, 512, 3, 1, 1, 1, True), (7, 7, 7, 512, 512, 3, 1, 1, 1, True),
                                   (13, 7, 7, 512, 512, 3, 1, 1, 0, False), (5, 15, 13, 256, 512, 3, 2, 1, 1, False),
                                   (9, 28, 28, 128, 256, 3, 2, 1, 1, False), (8, 28, 28, 128, 128, 3, 1, 1, 1, True),
-                                  (3, 14, 14, 1024, 256, 1, 1, 0, 1, False), (1, 56, 56, 64, 64, 3, 1, 1, 1, True)])
+                                  (3, 14, 14, 1024, 256, 1, 1, 0, 1, False), (7, 14, 14, 256, 512, 3, 2, 1, 1, False),
+                                  (2, 7, 7, 2048, 512, 1, 1, 0, 1, False), (1, 56, 56, 64, 64, 3, 1, 1, 1, True)])
 def test_packed_and_fragment_ordered_weights_give_the_same_bits(gpu_lib, case):
     # fs_test_conv has the fragment-ordered copy, the allocation-free entry point only the packed rows
     noalloc_equals_test_conv(*case, seed=5)
