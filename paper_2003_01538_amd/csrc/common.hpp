@@ -93,6 +93,9 @@ bool conv_tile_ok(Prec p, int t, const ConvArgs& a);         // the tile's kerne
 bool conv_tile_candidate(Prec p, int t, const ConvArgs& a);  // ... and is among its automatic choices
 bool conv_dma_ok(const ConvArgs& a);
 void launch_conv_dma(const ConvArgs& a, int bm, int bn, int waves, int wgm, int stages, hipStream_t s);
+bool conv_f32_ok(const ConvArgs& a);   // fp32: every planned layer
+int conv_f32_tile(const ConvArgs& a);  // ... and the tile that runs it
+void launch_conv_f32(const ConvArgs& a, int bm, int bn, int ks, hipStream_t s);
 bool conv_halo_ok(const ConvArgs& a, int th, int tw, int bn);
 bool conv_hs_ok(const ConvArgs& a);      // the streamed-weight halo kernel can run the layer
 bool conv_hs_chosen(const ConvArgs& a);  // ... and is its automatic choice

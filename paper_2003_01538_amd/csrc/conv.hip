@@ -12,8 +12,9 @@
 // row-contiguous, so bias, residual, ReLU and the rounding store are done
 // with 16-byte coalesced accesses.
 //
-// bf16: v_mfma_f32_16x16x32_bf16, BK = 64.  fp32: v_mfma_f32_16x16x4_f32,
-// BK = 32.  Four waves per workgroup in a 2 x 2 arrangement.  One launch
+// bf16: v_mfma_f32_16x16x32_bf16, BK = 64 (shapes the direct-load kernels do
+// not take; fp32 has a kernel of its own, conv_f32.hip).  Four waves per
+// workgroup in a 2 x 2 arrangement.  One launch
 // covers all Z models of a homogeneous group (the models' tensors sit at a
 // fixed stride), and the workgroup -> tile mapping keeps the N-tiles of an
 // M-tile on one XCD so that the A rows are re-read from that XCD's L2.
@@ -23,16 +24,6 @@
 #include <algorithm>
 
 namespace fs {
-
-template <int P> struct PT;
-template <> struct PT<BF16> {
-  using T = uint16_t;
-  static constexpr int BK = 64, KSTEP = 32;
-};
-template <> struct PT<F32> {
-  using T = float;
-  static constexpr int BK = 32, KSTEP = 4;
-};
 
 template <int BYTES> struct VecT;
 template <> struct VecT<16> { using T = uint4; };
@@ -57,10 +48,10 @@ __device__ __forceinline__ typename VecT<BYTES>::T buf_load(__amdgpu_buffer_rsrc
 
 // FAST: Cin is a multiple of BK, so every K-tile lies inside one filter tap
 // (ky, kx) and a contiguous channel range: the tap is wave-uniform.
-template <int P, int BM, int BN, int VEC, bool FAST>
+template <int BM, int BN, int VEC, bool FAST>
 __global__ void __launch_bounds__(NT, BM >= 256 ? 1 : 2) k_conv(ConvArgs a) {
-  using T = typename PT<P>::T;
-  constexpr int BK = PT<P>::BK, KSTEP = PT<P>::KSTEP;
+  using T = uint16_t;
+  constexpr int BK = 64, KSTEP = 32;
   constexpr int ES = sizeof(T);
   constexpr int RE = ROWB / ES;              // LDS row stride in elements
   constexpr int TM = BM / 2, TN = BN / 2;    // wave tile
@@ -191,33 +182,19 @@ __global__ void __launch_bounds__(NT, BM >= 256 ? 1 : 2) k_conv(ConvArgs a) {
     const T* Bs = reinterpret_cast<const T*>(smem + buf * STAGE + BM * ROWB);
 #pragma unroll
     for (int ks = 0; ks < BK / KSTEP; ++ks) {
-      if constexpr (P == BF16) {
-        bf16x8 af[FM], bfr[FN];
-        const int col = ks * KSTEP + (lane >> 4) * 8;
+      bf16x8 af[FM], bfr[FN];
+      const int col = ks * KSTEP + (lane >> 4) * 8;
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
-          af[i] = *reinterpret_cast<const bf16x8*>(As + (wm * TM + i * 16 + (lane & 15)) * RE + col);
+      for (int i = 0; i < FM; ++i)
+        af[i] = *reinterpret_cast<const bf16x8*>(As + (wm * TM + i * 16 + (lane & 15)) * RE + col);
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        bfr[j] = *reinterpret_cast<const bf16x8*>(Bs + (wn * TN + j * 16 + (lane & 15)) * RE + col);
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-          bfr[j] = *reinterpret_cast<const bf16x8*>(Bs + (wn * TN + j * 16 + (lane & 15)) * RE + col);
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-      } else {
-        float af[FM], bfr[FN];
-        const int col = ks * KSTEP + (lane >> 4);
-#pragma unroll
-        for (int i = 0; i < FM; ++i) af[i] = As[(wm * TM + i * 16 + (lane & 15)) * RE + col];
-#pragma unroll
-        for (int j = 0; j < FN; ++j) bfr[j] = Bs[(wn * TN + j * 16 + (lane & 15)) * RE + col];
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i], bfr[j], acc[i][j], 0, 0, 0);
-      }
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
     }
   };
 
@@ -271,30 +248,16 @@ __global__ void __launch_bounds__(NT, BM >= 256 ? 1 : 2) k_conv(ConvArgs a) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = Cs[row * CSTR + c8 * 8 + e] + bias[n + e];
     const int64_t o = (int64_t)m * a.Cout + n;
-    if constexpr (P == BF16) {
-      if (res) {
-        float r[8];
-        bf8_to_f8(*reinterpret_cast<const uint4*>(res + o), r);
+    if (res) {
+      float r[8];
+      bf8_to_f8(*reinterpret_cast<const uint4*>(res + o), r);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] += r[e];
-      }
-      if (a.relu)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
-      *reinterpret_cast<uint4*>(y + o) = f8_to_bf8(v);
-    } else {
-      if (res) {
-        float4 r0 = *reinterpret_cast<const float4*>(res + o);
-        float4 r1 = *reinterpret_cast<const float4*>(res + o + 4);
-        v[0] += r0.x; v[1] += r0.y; v[2] += r0.z; v[3] += r0.w;
-        v[4] += r1.x; v[5] += r1.y; v[6] += r1.z; v[7] += r1.w;
-      }
-      if (a.relu)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
-      *reinterpret_cast<float4*>(y + o) = make_float4(v[0], v[1], v[2], v[3]);
-      *reinterpret_cast<float4*>(y + o + 4) = make_float4(v[4], v[5], v[6], v[7]);
+      for (int e = 0; e < 8; ++e) v[e] += r[e];
     }
+    if (a.relu)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+    *reinterpret_cast<uint4*>(y + o) = f8_to_bf8(v);
   }
 }
 
@@ -336,9 +299,10 @@ static const ConvTile kTilesBF16[] = {
     {64, 128, 8, "bf16ks_64x128_w8_v8", 0, 8, 1, 4},
     {96, 128, 8, "bf16ks_96x128_w8_v8", 0, 8, 1, 4},
 };
-static const ConvTile kTilesF32[] = {
-    {64, 64, 4, "f32_64x64_v4"},
-    {64, 32, 4, "f32_64x32_v4"},
+static const ConvTile kTilesF32[] = {  // in the order of conv_f32_tile; wgm: groups of waves along the reduction
+    {64, 64, 4, "f32_64x64_v4", 0, 4, 1},
+    {32, 32, 4, "f32_32x32_k4_v4", 0, 4, 4},
+    {32, 32, 4, "f32_32x32_k8_v4", 0, 8, 8},
 };
 
 int conv_num_tiles(Prec p) {
@@ -350,6 +314,7 @@ const ConvTile& conv_tile(Prec p, int t) { return p == BF16 ? kTilesBF16[t] : kT
 bool conv_tile_ok(Prec p, int t, const ConvArgs& a) {
   if (t < 0 || t >= conv_num_tiles(p)) return false;
   const ConvTile& c = conv_tile(p, t);
+  if (p == F32) return conv_f32_ok(a);
   if (c.halo == 4) return p == BF16 && conv_ks_ok(a, c.bm, c.bn);
   if (c.halo == 3) return p == BF16 && conv_hr_ok(a, c.bm);
   if (c.halo == 2) return p == BF16 && conv_hs_ok(a);
@@ -363,6 +328,7 @@ bool conv_tile_ok(Prec p, int t, const ConvArgs& a) {
 // for the streamed-weight halo kernel).
 bool conv_tile_candidate(Prec p, int t, const ConvArgs& a) {
   if (!conv_tile_ok(p, t, a)) return false;
+  if (p == F32) return t == conv_f32_tile(a);
   if (conv_tile(p, t).halo == 4) return conv_ks_tile(p, a) == t;
   return conv_tile(p, t).halo < 2 || conv_hs_chosen(a);
 }
@@ -379,6 +345,7 @@ int conv_ks_tile(Prec p, const ConvArgs& a) {
 // Largest useful tile: prefer tiles that keep >= 2 workgroups per CU busy,
 // then the least padding waste, then the larger tile (more reuse per byte).
 int conv_pick_tile(Prec p, const ConvArgs& a, int num_cus, bool ks) {
+  if (p == F32) return conv_f32_ok(a) ? conv_f32_tile(a) : -1;
   const int few = ks ? conv_ks_tile(p, a) : -1;
   if (few >= 0) return few;
   int fam = -1;
@@ -400,13 +367,13 @@ int conv_pick_tile(Prec p, const ConvArgs& a, int num_cus, bool ks) {
   return best;
 }
 
-template <int P, int BM, int BN, int VEC>
+template <int BM, int BN, int VEC>
 static void launch_t(const ConvArgs& a, hipStream_t s) {
   const int tiles = ((a.M + BM - 1) / BM) * ((a.Cout + BN - 1) / BN) * a.Z;
-  if (a.Cin % PT<P>::BK == 0)
-    hipLaunchKernelGGL((k_conv<P, BM, BN, VEC, true>), dim3(tiles), dim3(NT), 0, s, a);
+  if (a.Cin % 64 == 0)
+    hipLaunchKernelGGL((k_conv<BM, BN, VEC, true>), dim3(tiles), dim3(NT), 0, s, a);
   else
-    hipLaunchKernelGGL((k_conv<P, BM, BN, VEC, false>), dim3(tiles), dim3(NT), 0, s, a);
+    hipLaunchKernelGGL((k_conv<BM, BN, VEC, false>), dim3(tiles), dim3(NT), 0, s, a);
 }
 
 void launch_conv(const ConvArgs& a, Prec p, int tile, hipStream_t s, bool reduce) {
@@ -436,20 +403,17 @@ void launch_conv(const ConvArgs& a, Prec p, int tile, hipStream_t s, bool reduce
   }
   if (p == BF16) {
     switch (tile) {
-      case 0: launch_t<BF16, 128, 128, 8>(a, s); break;
-      case 1: launch_t<BF16, 128, 64, 8>(a, s); break;
-      case 2: launch_t<BF16, 64, 64, 8>(a, s); break;
-      case 3: launch_t<BF16, 128, 64, 4>(a, s); break;
-      case 4: launch_t<BF16, 64, 64, 4>(a, s); break;
-      case 5: launch_t<BF16, 256, 64, 8>(a, s); break;
+      case 0: launch_t<128, 128, 8>(a, s); break;
+      case 1: launch_t<128, 64, 8>(a, s); break;
+      case 2: launch_t<64, 64, 8>(a, s); break;
+      case 3: launch_t<128, 64, 4>(a, s); break;
+      case 4: launch_t<64, 64, 4>(a, s); break;
+      case 5: launch_t<256, 64, 8>(a, s); break;
       default: break;
     }
   } else {
-    switch (tile) {
-      case 0: launch_t<F32, 64, 64, 4>(a, s); break;
-      case 1: launch_t<F32, 64, 32, 4>(a, s); break;
-      default: break;
-    }
+    const ConvTile& c = conv_tile(p, tile);
+    launch_conv_f32(a, c.bm, c.bn, c.wgm, s);
   }
 }
 

@@ -61,14 +61,6 @@ constexpr int HS_RI = 8;                   // residual loads per lane and tile
 constexpr int HS_SI = 8;                   // output stores per lane and tile
 constexpr int HS_WSLOT = HS_BN * ROW;      // one tap's weights: 128 rows x 128 bytes
 
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
-}
-
 // Patch instructions per wave in slice u of a chunk's nine slices.
 template <int NPBW>
 constexpr int hs_ps(int u) { return NPBW / 9 + (u < NPBW % 9 ? 1 : 0); }

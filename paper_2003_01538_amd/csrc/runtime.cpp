@@ -973,11 +973,11 @@ const std::vector<std::vector<int>>& tiles_for(fs_ensemble* e, int B, hipStream_
         e->workspace_bytes += (int64_t)e->conv_partial.bytes;
         a.partial = static_cast<float*>(e->conv_partial.p);
       }
-      // a layer of few tiles runs with its reduction split over a workgroup's
-      // waves, in the tile its rule names: nothing to time (FS_TUNE=1, which
-      // times every layer, times that one tile)
+      // an fp32 layer, and a bf16 layer of few tiles (its reduction split over
+      // a workgroup's waves), run in the one tile their rules name: nothing to
+      // time (FS_TUNE=1, which times every layer, times that tile)
       const int ruled = conv_pick_tile(e->prec, a, e->num_cus);
-      if (e->tune != 1 && ruled >= 0 && conv_tile_family(conv_tile(e->prec, ruled)) == 4) {
+      if (e->tune != 1 && ruled >= 0 && (e->prec == F32 || conv_tile_family(conv_tile(e->prec, ruled)) == 4)) {
         choice[gi][li] = ruled;
         continue;
       }
