@@ -321,6 +321,19 @@ fs_status fs_test_conv(const float *in, int32_t B, int32_t H, int32_t W, int32_t
                        int32_t kh, int32_t kw, int32_t stride, int32_t pad, int32_t relu,
                        int32_t precision, int32_t tile, float *out, int32_t device);
 
+/* A widening 1x1 conv and the narrowing 1x1 conv that reads it, bf16, both
+ * with ReLU: y = relu(w1 . [in | in2 at stride2] + bias1 + res), out =
+ * relu(w2 . y + bias2); in2 (a projection shortcut's input) or res, or
+ * neither.  w1 [N1][Cin + Cin2], w2 [N2][N1], y [B][H][W][N1], out
+ * [B][H][W][N2].  fused: in the one launch the ensemble uses for it where
+ * that is faster (FS_ERR_UNSUPPORTED for channel counts it does not take);
+ * otherwise as two launches of the implicit GEMM. */
+fs_status fs_test_conv_pair(const float *in, int32_t B, int32_t H, int32_t W, int32_t Cin,
+                            const float *in2, int32_t H2, int32_t W2, int32_t Cin2, int32_t stride2,
+                            const float *w1, const float *bias1, const float *res, int32_t N1,
+                            const float *w2, const float *bias2, int32_t N2, int32_t fused, float *y,
+                            float *out, int32_t device);
+
 /* The ResNet stem as the ensemble runs it in bf16: conv 7x7 / stride 2 /
  * pad 3 from 3 channels to 64 (in its space-to-depth form), + bias, ReLU,
  * bf16 rounding, then max pool 3x3 / stride 2 / pad 1 (He et al., the

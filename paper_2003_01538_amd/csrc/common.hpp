@@ -108,6 +108,11 @@ bool conv_ks_ok(const ConvArgs& a, int bm, int bn);
 int conv_ks_pick(const ConvArgs& a, int* bm, int* bn);
 int conv_ks_tile(Prec p, const ConvArgs& a);  // the same as an index of conv_tile
 void launch_conv_ks(const ConvArgs& a, int bm, int bn, hipStream_t s);
+// A widening 1x1 conv (a) and the narrowing 1x1 conv that reads it (d) in one
+// launch, which writes both outputs.
+bool conv_pair_ok(const ConvArgs& a, const ConvArgs& d);      // the kernel takes the two layers
+bool conv_pair_chosen(const ConvArgs& a, const ConvArgs& d, int num_cus);  // ... and is faster than two launches
+void launch_conv_pair(const ConvArgs& a, const ConvArgs& d, hipStream_t s);
 // Space-to-depth ResNet stem (4x4/1/p2 on 16 channels, 64 outputs, ReLU)
 // fused with the following 3x3/2/p1 max pool; y receives the pooled tensor.
 bool conv_stem_pool_ok(const ConvArgs& a);

@@ -140,6 +140,7 @@ struct LayerPlan {
   bool s2d = false;       // first conv rewritten on the space-to-depth input
   bool pool_fused = false;  // conv: also applies the next layer's 3x3/2 max pool, writes the pooled tensor
   bool fused_away = false;  // max pool: done by the conv before it (no launch, shares its slot)
+  bool pair = false;        // 1x1 conv that may run in one launch with the next layer (conv_pair_chosen)
   bool gap_only = false;    // conv whose only reader is the global average pool right after it
   // projection shortcut (bf16): a 1x1 conv read only as the residual of one
   // later conv is computed inside that conv's launch as the tail of its
@@ -557,6 +558,20 @@ void plan_group(fs_ensemble* e, const fs_ensemble_desc* d, Group& g) {
       folded_into[dd] = i;
       last_use[D.src] = std::max(last_use[D.src], i);  // read by the conv itself now
     }
+  // a 1x1 conv and the 1x1 conv right after it that reads it may run in one
+  // launch, by batch size: the second's output then must not share a slot
+  // with what the first reads
+  if (e->prec == BF16)
+    for (int i = 0; i + 1 < n - 1; ++i) {
+      const fs_layer &L = s.layers[i], &N = s.layers[i + 1];
+      auto plain = [](const fs_layer& l) {
+        return l.op == FS_OP_CONV && l.kh == 1 && l.kw == 1 && l.stride == 1 && l.pad == 0 && l.relu && l.src >= 0;
+      };
+      if (!plain(L) || !plain(N) || N.src != i || N.residual_src >= 0) continue;
+      g.layers[i].pair = true;
+      for (int r : {L.src, L.residual_src, proj_of[i] >= 0 ? s.layers[proj_of[i]].src : -1})
+        if (r >= 0) last_use[r] = std::max(last_use[r], i + 1);
+    }
   // slots: greedy reuse of freed buffers
   std::vector<int> slot_busy_until;  // layer index of last reader, per slot
   std::vector<int64_t>& slot_elems = g.slot_elems;
@@ -907,6 +922,15 @@ ConvArgs conv_args(fs_ensemble* e, Group& g, const LayerPlan& P, int B, void* y,
   return a;
 }
 
+// Whether layer li (whose arguments are a) runs in one launch with the next
+// layer at this batch size, and that layer's arguments.
+bool pair_args(fs_ensemble* e, Group& g, const LayerPlan& P, int li, int B, const ConvArgs& a, ConvArgs* d) {
+  if (!P.pair) return false;
+  const LayerPlan& N = g.layers[li + 1];
+  *d = conv_args(e, g, N, B, slot_ptr(g, N.out_slot), (int64_t)g.slot_elems[N.out_slot] * e->max_batch);
+  return conv_pair_chosen(a, *d, e->num_cus);
+}
+
 int batch_bucket(int B, int max_batch) {
   int b = 1;
   while (b < B) b <<= 1;
@@ -1121,6 +1145,20 @@ void run_pass(fs_ensemble* e, const uint8_t* d_pixels, const ImageDesc* d_desc, 
         case FS_OP_CONV: {
           if (P.proj_into >= 0) break;  // runs inside its block's last conv
           ConvArgs a = conv_args(e, g, P, B, y, y_ms);
+          ConvArgs d;
+          if (pair_args(e, g, P, (int)li, B, a, &d)) {
+            const LayerPlan& N = g.layers[li + 1];
+            launch.M = a.M; launch.N = a.Cout; launch.K = P.kreal;
+            launch.kernel = "conv_pair_1x1";
+            const double flops = 2.0 * a.M * (double)a.Cout * (P.kreal + d.Cout) * g.Z;
+            const double px = (double)P.kreal + a.Cout * (a.res ? 2.0 : 1.0) + d.Cout;
+            const double bytes = (px * a.M + (double)a.Cout * (P.kreal + d.Cout)) * esz * g.Z;
+            launch(K_CONV, flops, bytes, 1, [&] { launch_conv_pair(a, d, s); });
+            dbg_capture(e, g, (int)li, y, y_ms, P.out.elems(), esz, B, s);
+            dbg_capture(e, g, (int)li + 1, d.y, d.y_mstride, N.out.elems(), esz, B, s);
+            skip_next = true;
+            break;
+          }
           // only the implicit GEMM splits K over workgroups
           if (P.pool_fused || !conv_tile_direct(conv_tile(p, tiles[gi][li]))) a.split = 1;
           if (conv_partial_floats(a) * 4 > (g.conv_partial.p ? g.conv_partial.bytes : e->conv_partial.bytes))
@@ -1231,6 +1269,12 @@ int launches_per_pass(fs_ensemble* e) {
         n += fc_launches(fc_pick_split(e->prec, e->max_batch, P.K, P.out.C, g.Z, e->num_cus));
       } else if (P.op == FS_OP_CONV && P.proj_into < 0) {
         const ConvArgs a = conv_args(e, g, P, e->max_batch, nullptr, 0);
+        ConvArgs d;
+        if (pair_args(e, g, P, (int)li, e->max_batch, a, &d)) {
+          n += 1;
+          skip_next = true;
+          continue;
+        }
         const int gi = (int)(&g - e->groups.data());
         const int tile = tl ? (*tl)[gi][li] : P.pool_fused ? -1 : conv_pick_tile(e->prec, a, e->num_cus);
         n += (!P.pool_fused && a.split > 1 && tile >= 0 && conv_tile_direct(conv_tile(e->prec, tile))) ? 2 : 1;
@@ -2097,6 +2141,65 @@ fs_status fs_test_conv(const float* in, int32_t B, int32_t H, int32_t W, int32_t
   return guarded(nullptr, [&] {
     run_test_conv(in, B, H, W, Cin, w, bias, res, Cout, kh, kw, stride, pad, relu, precision, tile, out, device,
                   false);
+  });
+}
+
+fs_status fs_test_conv_pair(const float* in, int32_t B, int32_t H, int32_t W, int32_t Cin, const float* in2,
+                            int32_t H2, int32_t W2, int32_t Cin2, int32_t stride2, const float* w1,
+                            const float* bias1, const float* res, int32_t N1, const float* w2, const float* bias2,
+                            int32_t N2, int32_t fused, float* y, float* out, int32_t device) {
+  return guarded(nullptr, [&] {
+    if (!in || !w1 || !bias1 || !w2 || !bias2 || !y || !out || B < 1 || H < 1 || W < 1 || Cin < 1 || N1 < 1 ||
+        N2 < 1 || (in2 && (H2 < 1 || W2 < 1 || Cin2 < 1 || stride2 < 1)))
+      fail(FS_ERR_INVALID, "bad conv pair arguments");
+    if (Cin % 64 || N1 % 64 || N2 % 32 || (in2 && Cin2 % 64)) fail(FS_ERR_UNSUPPORTED, "channels not in steps of 64");
+    if (in2 && ((H - 1) * stride2 >= H2 || (W - 1) * stride2 >= W2)) fail(FS_ERR_INVALID, "shortcut input too small");
+    const int64_t m = (int64_t)B * H * W;
+    if (m * std::max({Cin, N1, N2}) * 2 >= (int64_t(1) << 31)) fail(FS_ERR_UNSUPPORTED, "tensor exceeds 2 GiB");
+    set_device(device);
+    TmpDev t;
+    ConvArgs a{}, d{};
+    auto weights = [&](ConvArgs& c, const float* w, const float* b) {
+      std::vector<uint16_t> h((size_t)c.Cout * c.Kp), f(h.size());
+      for (size_t i = 0; i < h.size(); ++i) h[i] = host_bf16(w[i]);
+      conv_frag_order(h.data(), c.Cout, c.Kp, f.data());
+      void *dw = t.alloc(h.size() * 2), *df = t.alloc(h.size() * 2), *db = t.alloc(c.Cout * 4);
+      HIPCHK(hipMemcpy(dw, h.data(), h.size() * 2, hipMemcpyHostToDevice));
+      HIPCHK(hipMemcpy(df, f.data(), f.size() * 2, hipMemcpyHostToDevice));
+      HIPCHK(hipMemcpy(db, b, c.Cout * 4, hipMemcpyHostToDevice));
+      c.w = dw; c.wf = df; c.bias = static_cast<const float*>(db);
+    };
+    a.x = upload_as(t, in, m * Cin, BF16);
+    a.y = t.alloc((size_t)m * N1 * 2);
+    a.B = B; a.H = a.Ho = H; a.W = a.Wo = W; a.Cin = Cin; a.Cout = N1;
+    a.kh = a.kw = a.stride = 1; a.pad = 0; a.relu = 1; a.M = (int)m; a.Z = 1;
+    a.K = a.Kp = Cin + (in2 ? Cin2 : 0);
+    if (in2) {
+      a.x2 = upload_as(t, in2, (int64_t)B * H2 * W2 * Cin2, BF16);
+      a.H2 = H2; a.W2 = W2; a.Cin2 = Cin2; a.stride2 = stride2; a.K1 = Cin;
+    }
+    if (res) a.res = upload_as(t, res, m * N1, BF16);
+    weights(a, w1, bias1);
+    d = a;
+    d.x = a.y; d.y = t.alloc((size_t)m * N2 * 2); d.res = nullptr; d.x2 = nullptr; d.K1 = 0;
+    d.Cin = N1; d.K = d.Kp = N1; d.Cout = N2;
+    weights(d, w2, bias2);
+    if (fused) {
+      if (!conv_pair_ok(a, d)) fail(FS_ERR_UNSUPPORTED, "not a pair of convs the kernel takes");
+      launch_conv_pair(a, d, nullptr);
+    } else {  // the implicit GEMM, unsplit
+      int tile = -1;
+      for (int i = 0; i < conv_num_tiles(BF16); ++i)
+        if (std::strcmp(conv_tile(BF16, i).name, "bf16dma3_64x64_w4_v8") == 0) tile = i;
+      for (const ConvArgs* c : {&a, &d}) {
+        if (tile < 0 || !conv_tile_ok(BF16, tile, *c)) fail(FS_ERR_UNSUPPORTED, "no implicit GEMM takes this conv");
+        launch_conv(*c, BF16, tile, nullptr);
+      }
+    }
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipDeviceSynchronize());
+    download_as(y, a.y, m * N1, BF16);
+    download_as(out, d.y, m * N2, BF16);
   });
 }
 

@@ -121,6 +121,9 @@ SIGNATURES = [
                                     _fp, _fp, _fp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                                     ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                                     ctypes.c_int32, _fp, ctypes.c_int32]),
+    ("fs_test_conv_pair", ctypes.c_int, [_fp] + [ctypes.c_int32] * 4 + [_fp] + [ctypes.c_int32] * 4 +
+                                        [_fp, _fp, _fp, ctypes.c_int32, _fp, _fp, ctypes.c_int32, ctypes.c_int32,
+                                         _fp, _fp, ctypes.c_int32]),
     ("fs_test_stem_pool", ctypes.c_int, [_fp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, _fp, _fp, _fp,
                                          ctypes.c_int32]),
     ("fs_test_maxpool", ctypes.c_int, [_fp] + [ctypes.c_int32] * 8 + [_fp, ctypes.c_int32]),
@@ -415,6 +418,18 @@ def fs_test_conv(x, w, bias, res, stride, pad, relu, precision, tile=-1, device=
     _check(load().fs_test_conv(_f(x), B, H, W, Cin, _f(w), _f(b), _f(r), Cout, kh, kw, stride, pad,
                                int(relu), precision, tile, _f(out), device))
     return out
+
+
+def fs_test_conv_pair(x, x2, stride2, w1, b1, res, w2, b2, fused, device=0):
+    f = lambda t: None if t is None else np.ascontiguousarray(t, np.float32)
+    x, x2, w1, b1, res, w2, b2 = map(f, (x, x2, w1, b1, res, w2, b2))
+    B, H, W, Cin = x.shape
+    H2, W2, Cin2 = (0, 0, 0) if x2 is None else x2.shape[1:]
+    N1, N2 = w1.shape[0], w2.shape[0]
+    y, out = np.zeros((B, H, W, N1), np.float32), np.zeros((B, H, W, N2), np.float32)
+    _check(load().fs_test_conv_pair(_f(x), B, H, W, Cin, _f(x2), H2, W2, Cin2, stride2, _f(w1), _f(b1), _f(res), N1,
+                                    _f(w2), _f(b2), N2, int(fused), _f(y), _f(out), device))
+    return y, out
 
 
 def fs_test_stem_pool(x, w, bias, device=0):
