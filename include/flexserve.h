@@ -345,6 +345,14 @@ fs_status fs_test_conv_pair(const float *in, int32_t B, int32_t H, int32_t W, in
 fs_status fs_test_stem_pool(const float *in, int32_t B, int32_t H, int32_t W, const float *w,
                             const float *bias, float *out, int32_t device);
 
+/* The first layers of a VGG-type network as the ensemble runs them in bf16:
+ * conv 3x3 / stride 1 / pad 1 from 3 channels to 64, + bias, ReLU, bf16
+ * rounding, then max pool 2x2 / stride 2, in one kernel.  in [B][H][W][3]
+ * (H, W even, else FS_ERR_UNSUPPORTED), w [64][3][3][3], bias [64] or NULL,
+ * out [B][H/2][W/2][64]. */
+fs_status fs_test_first_pool(const float *in, int32_t B, int32_t H, int32_t W, const float *w,
+                             const float *bias, float *out, int32_t device);
+
 fs_status fs_test_maxpool(const float *in, int32_t B, int32_t H, int32_t W, int32_t C,
                           int32_t k, int32_t stride, int32_t pad, int32_t precision,
                           float *out, int32_t device);

@@ -113,6 +113,10 @@ void launch_conv_ks(const ConvArgs& a, int bm, int bn, hipStream_t s);
 bool conv_pair_ok(const ConvArgs& a, const ConvArgs& d);      // the kernel takes the two layers
 bool conv_pair_chosen(const ConvArgs& a, const ConvArgs& d, int num_cus);  // ... and is faster than two launches
 void launch_conv_pair(const ConvArgs& a, const ConvArgs& d, hipStream_t s);
+// First 3x3 conv (3 channels to 64, ReLU) fused with the following 2x2/2 max
+// pool; y receives the pooled tensor.
+bool conv_first_pool_ok(const ConvArgs& a);
+void launch_conv_first_pool(const ConvArgs& a, int num_cus, hipStream_t s);
 // Space-to-depth ResNet stem (4x4/1/p2 on 16 channels, 64 outputs, ReLU)
 // fused with the following 3x3/2/p1 max pool; y receives the pooled tensor.
 bool conv_stem_pool_ok(const ConvArgs& a);

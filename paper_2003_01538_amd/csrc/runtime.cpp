@@ -138,7 +138,8 @@ struct LayerPlan {
   int in_slot = SLOT_INPUT, res_slot = -1, out_slot = -1;
   bool last = false;
   bool s2d = false;       // first conv rewritten on the space-to-depth input
-  bool pool_fused = false;  // conv: also applies the next layer's 3x3/2 max pool, writes the pooled tensor
+  bool pool_fused = false;  // conv: also applies the next layer's max pool, writes the pooled tensor
+                            // (s2d: the 3x3/2 of a ResNet stem; otherwise the 2x2/2 after a first 3x3 conv)
   bool fused_away = false;  // max pool: done by the conv before it (no launch, shares its slot)
   bool pair = false;        // 1x1 conv that may run in one launch with the next layer (conv_pair_chosen)
   bool gap_only = false;    // conv whose only reader is the global average pool right after it
@@ -616,6 +617,13 @@ void plan_group(fs_ensemble* e, const fs_ensemble_desc* d, Group& g) {
           const fs_layer& Nx = s.layers[i + 1];  // a max pool that is the conv's only reader
           P.pool_fused = Nx.op == FS_OP_MAXPOOL && Nx.src == i && Nx.kh == 3 && Nx.kw == 3 && Nx.stride == 2 &&
                          Nx.pad == 1 && last_use[i] == i + 1;
+        }
+        if (!P.s2d && e->prec == BF16 && L.src < 0 && L.cin == 3 && L.kh == 3 && L.kw == 3 && L.stride == 1 &&
+            L.pad == 1 && L.relu && L.residual_src < 0 && L.cout == 64 && P.out.H % 2 == 0 && P.out.W % 2 == 0 &&
+            i + 1 < n - 1) {
+          const fs_layer& Nx = s.layers[i + 1];
+          P.pool_fused = Nx.op == FS_OP_MAXPOOL && Nx.src == i && Nx.kh == 2 && Nx.kw == 2 && Nx.stride == 2 &&
+                         Nx.pad == 0 && last_use[i] == i + 1;
         }
         break;
       case FS_OP_MAXPOOL:
@@ -1165,7 +1173,7 @@ void run_pass(fs_ensemble* e, const uint8_t* d_pixels, const ImageDesc* d_desc, 
             fail(FS_ERR_INTERNAL, "split-K scratch too small for this batch size");
           const int tile = tiles[gi][li];
           launch.M = a.M; launch.N = a.Cout; launch.K = P.kreal;
-          launch.kernel = P.pool_fused ? "stem_s2d_conv_maxpool" : conv_tile(p, tile).name;
+          launch.kernel = P.pool_fused ? P.s2d ? "stem_s2d_conv_maxpool" : "first_conv_maxpool" : conv_tile(p, tile).name;
           const double kreal = (double)P.kreal;
           const double flops = 2.0 * a.M * a.Cout * kreal * g.Z;
           const double in_b = (double)B * P.in.H * P.in.W * P.in_c_real * (P.s2d ? 4 : 1) * esz *
@@ -1175,7 +1183,7 @@ void run_pass(fs_ensemble* e, const uint8_t* d_pixels, const ImageDesc* d_desc, 
           const double bytes = in_b + proj_b + ((double)a.Cout * kreal * esz + out_px * a.Cout * esz * (a.res ? 2 : 1)) * g.Z;
           const size_t yes = P.last ? 4 : esz;
           if (P.pool_fused) {
-            launch(K_CONV, flops, bytes, 1, [&] { launch_conv_stem_pool(a, s); });
+            launch(K_CONV, flops, bytes, 1, [&] { P.s2d ? launch_conv_stem_pool(a, s) : launch_conv_first_pool(a, e->num_cus, s); });
             dbg_capture(e, g, (int)li + 1, y, y_ms, g.layers[li + 1].out.elems(), esz, B, s);
           } else if (P.gap_only && p == BF16 && conv_tile_direct(conv_tile(p, tile)) && conv_reduce_gap_ok(a)) {
             // the split-K completion also takes the average pool of the next layer
@@ -2112,6 +2120,14 @@ static void run_test_conv(const float* in, int32_t B, int32_t H, int32_t W, int3
     a.B = B; a.H = gH; a.W = gW; a.Cin = gC; a.Ho = Ho; a.Wo = Wo; a.Cout = Cout;
     a.kh = gk; a.kw = gk; a.stride = gs; a.pad = gp; a.relu = relu ? 1 : 0;
     a.K = K; a.Kp = Kp; a.M = B * Ho * Wo; a.Z = 1;
+    if (stem_pool && !use_s2d) {
+      if (!conv_first_pool_ok(a)) fail(FS_ERR_UNSUPPORTED, "not a first conv the fused kernel takes");
+      launch_conv_first_pool(a, num_cus_of(device), nullptr);
+      HIPCHK(hipGetLastError());
+      HIPCHK(hipDeviceSynchronize());
+      download_as(out, dy, (int64_t)B * (Ho / 2) * (Wo / 2) * Cout, p);
+      return;
+    }
     if (stem_pool) {
       if (!use_s2d || !conv_stem_pool_ok(a)) fail(FS_ERR_UNSUPPORTED, "not a space-to-depth stem the fused kernel takes");
       const int64_t npool = (int64_t)B * ((Ho - 1) / 2 + 1) * ((Wo - 1) / 2 + 1) * Cout;
@@ -2208,6 +2224,13 @@ fs_status fs_test_stem_pool(const float* in, int32_t B, int32_t H, int32_t W, co
   return guarded(nullptr, [&] {
     if (H % 2 || W % 2) fail(FS_ERR_UNSUPPORTED, "the space-to-depth stem needs even H and W");
     run_test_conv(in, B, H, W, 3, w, bias, nullptr, 64, 7, 7, 2, 3, 1, FS_BF16, -1, out, device, true);
+  });
+}
+
+fs_status fs_test_first_pool(const float* in, int32_t B, int32_t H, int32_t W, const float* w, const float* bias,
+                             float* out, int32_t device) {
+  return guarded(nullptr, [&] {
+    run_test_conv(in, B, H, W, 3, w, bias, nullptr, 64, 3, 3, 1, 1, 1, FS_BF16, -1, out, device, true);
   });
 }
 

@@ -1,0 +1,38 @@
+"""A network's first 3x3 convolution fused with its 2x2 max pool: against the
+CPU oracle and the two layers run separately, at sizes around the eight
+windows a wave takes at a time and the four rows of a workgroup."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2003_01538_amd import flexserve as fsb
+from tests.test_gpu_kernels import BF16, assert_bf16_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,H,W", [(1, 2, 2), (2, 6, 16), (3, 10, 18), (1, 34, 14), (5, 18, 66), (1, 224, 224)])
+def test_first_conv_maxpool_fused(gpu_lib, B, H, W):
+    rng = np.random.default_rng(H * 1000 + W)
+    x = oracle.round_bf16(rng.standard_normal((B, H, W, 3)).astype(np.float32))
+    w = oracle.round_bf16((rng.standard_normal((64, 3, 3, 3)) * np.sqrt(2.0 / 27)).astype(np.float32))
+    b = (rng.standard_normal(64) * 0.1).astype(np.float32)
+    g = fsb.fs_test_first_pool(x, w, b)
+    c, ab = oracle.conv2d(x, w, b, 1, 1, 1, None, "bf16", want_abs=True)
+    # the pooled value may be any window element that the sums' order brings to the top
+    assert_bf16_close(g, oracle.maxpool(c, 2, 2, 0), oracle.maxpool(ab, 2, 2, 0), what=f"oracle {B}x{H}x{W}")
+    sep = fsb.fs_test_maxpool(fsb.fs_test_conv(x, w, b, None, 1, 1, 1, BF16), 2, 2, 0, BF16)
+    assert_bf16_close(g, sep, oracle.maxpool(ab, 2, 2, 0), what=f"two layers {B}x{H}x{W}")
+    # infinities reach the same outputs, and a sum that is not a number leaves the ReLU as zero
+    x[0, 0, 0, 0], x[-1, -1, -1, 1] = np.inf, -np.inf
+    g = fsb.fs_test_first_pool(x, w, b)
+    sep = fsb.fs_test_maxpool(fsb.fs_test_conv(x, w, b, None, 1, 1, 1, BF16), 2, 2, 0, BF16)
+    assert np.array_equal(np.isinf(g), np.isinf(sep)) and not np.isnan(g).any() and np.isinf(g).any()
+
+
+def test_odd_maps_are_refused(gpu_lib):
+    z = lambda *s: np.zeros(s, np.float32)
+    for h, w in [(7, 8), (8, 7)]:
+        with pytest.raises(fsb.FsError) as e:
+            fsb.fs_test_first_pool(z(1, h, w, 3), z(64, 3, 3, 3), z(64))
+        assert e.value.status == fsb.FS_ERR_UNSUPPORTED
