@@ -22,6 +22,9 @@
 #include "device.hpp"
 
 #include <algorithm>
+#include <array>
+#include <cmath>
+#include <cstring>
 
 namespace fs {
 
@@ -342,19 +345,73 @@ int conv_ks_tile(Prec p, const ConvArgs& a) {
   return -1;
 }
 
-// Largest useful tile: prefer tiles that keep >= 2 workgroups per CU busy,
-// then the least padding waste, then the larger tile (more reuse per byte).
+// Time in us of a layer on an LDS-DMA tile, for the tiles worth choosing
+// without timing them: a + b nk + (c nk + d) ceil(n) + (e nk + f) n, with nk
+// K-tiles per workgroup and n workgroups per CU (at least one), each
+// coefficient fitted (non-negative, least squares of the relative error, 4 to
+// 13 % rms) to 234 measured launches: 3x3 and 1x1 layers of 64 to 2048
+// channels, stride 1 and 2, maps of 7 to 112, B = 1 to 32, with and without
+// the weights in fragment order.  The tile it picks is on average 2.5 % slower
+// than the fastest of all twenty; a rule by the tiles' fill and reuse was 16 %
+// (1x1, 64 -> 256 with a residual on 56x56, B = 32: 26 us on 64x128 instead of
+// 32 on 256x256; 3x3, 64 -> 128 on 112x112: 65 instead of 92).
+struct DmaCost {
+  const char* tile;
+  bool frag;  // with (true) or without fragment-ordered weights; the other tiles: the same either way
+  float a, b, c, d, e, f;
+};
+static const DmaCost kDmaCost[] = {
+    {"bf16dma3_64x64_w4_v8", true, 2.54f, 0.22f, 0.14f, 0.56f, 0.f, 0.52f},
+    {"bf16dma2_64x128_w4_v8", true, 2.61f, 0.19f, 0.19f, 0.78f, 0.f, 0.82f},
+    {"bf16dma1_64x128_w4_v8", true, 2.84f, 0.46f, 0.01f, 1.13f, 0.15f, 0.19f},
+    {"bf16dma2_128x64_w4_v8", true, 2.68f, 0.23f, 0.17f, 1.00f, 0.f, 0.82f},
+    {"bf16dma1_128x64_w4_v8", true, 2.92f, 0.46f, 0.04f, 1.12f, 0.09f, 0.52f},
+    {"bf16dma2_96x128_w4m1_v8", true, 3.14f, 0.36f, 0.03f, 0.97f, 0.15f, 1.07f},
+    {"bf16dma2_96x128_w4m1_v8", false, 2.19f, 0.30f, 0.08f, 1.17f, 0.18f, 1.57f},
+    {"bf16dma2_128x128_w4_v8", true, 2.24f, 0.37f, 0.14f, 1.00f, 0.13f, 2.51f},
+    {"bf16dma1_128x128_w4_v8", true, 3.27f, 0.64f, 0.f, 1.13f, 0.21f, 1.66f},
+};
+
+static int dma_pick(const ConvArgs& a, int num_cus) {
+  constexpr int N = sizeof(kDmaCost) / sizeof(DmaCost);
+  static const std::array<int, N> index = [] {
+    std::array<int, N> ix{};
+    for (int i = 0; i < N; ++i)
+      while (std::strcmp(conv_tile(BF16, ix[i]).name, kDmaCost[i].tile) != 0) ++ix[i];
+    return ix;
+  }();
+  int best = -1;
+  float best_t = 0.f;
+  for (int i = 0; i < N; ++i) {
+    const DmaCost& k = kDmaCost[i];
+    const int t = index[i];
+    const ConvTile& c = conv_tile(BF16, t);
+    if (c.wgm == 1 && k.frag != (a.wf != nullptr)) continue;
+    const float nk = (float)(a.Kp / 64) / a.split;
+    const float n = std::max(1.f, (float)((a.M + c.bm - 1) / c.bm) * ((a.Cout + c.bn - 1) / c.bn) * a.Z * a.split / num_cus);
+    const float us = k.a + k.b * nk + (k.c * nk + k.d) * std::ceil(n) + (k.e * nk + k.f) * n;
+    if (best < 0 || us < best_t) { best = t; best_t = us; }
+  }
+  return best;
+}
+
+// The LDS-DMA tiles by dma_pick.  Within the other families the largest
+// useful tile: prefer tiles that keep >= 2 workgroups per CU busy, then the
+// least padding waste, then the larger tile (more reuse per byte).
 int conv_pick_tile(Prec p, const ConvArgs& a, int num_cus, bool ks) {
   if (p == F32) return conv_f32_ok(a) ? conv_f32_tile(a) : -1;
   const int few = ks ? conv_ks_tile(p, a) : -1;
   if (few >= 0) return few;
-  int fam = -1;
+  const bool dma = conv_dma_ok(a);  // one answer for all of that family's tiles
+  int fam = dma ? 1 : -1;
   for (int t = 0; t < conv_num_tiles(p); ++t)
-    if (conv_tile(p, t).halo != 4 && conv_tile_candidate(p, t, a)) fam = std::max(fam, conv_tile_family(conv_tile(p, t)));
+    if (conv_tile(p, t).halo != 4 && conv_tile_family(conv_tile(p, t)) > fam && !conv_tile_direct(conv_tile(p, t)) &&
+        conv_tile_candidate(p, t, a)) fam = std::max(fam, conv_tile_family(conv_tile(p, t)));
+  if (fam == 1) return dma_pick(a, num_cus);
   int best = -1;
   double best_score = -1;
   for (int t = 0; t < conv_num_tiles(p); ++t) {
-    if (conv_tile(p, t).halo == 4 || !conv_tile_candidate(p, t, a) || conv_tile_family(conv_tile(p, t)) != fam) continue;
+    if (conv_tile_family(conv_tile(p, t)) != fam || !conv_tile_candidate(p, t, a)) continue;
     const ConvTile& c = conv_tile(p, t);
     const double tm = (a.M + c.bm - 1) / c.bm, tn = (a.Cout + c.bn - 1) / c.bn;
     const double wgs = tm * tn * a.Z;
