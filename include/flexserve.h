@@ -366,6 +366,13 @@ fs_status fs_test_fc(const float *in, int32_t B, int32_t K, const float *w, cons
                      int32_t N, int32_t relu, int32_t precision, int32_t out_storage,
                      float *out, int32_t device);
 
+/* The global average pool of in [B][H][W][K] (pooled [B][K]) and the layer
+ * that reads it (out [B][N] fp32, as fs_test_fc) in the one launch that small
+ * batches take; FS_ERR_UNSUPPORTED for sizes that run as two. */
+fs_status fs_test_gap_fc(const float *in, int32_t B, int32_t H, int32_t W, int32_t K, const float *w,
+                         const float *bias, int32_t N, int32_t relu, int32_t precision, float *pooled,
+                         float *out, int32_t device);
+
 /* Softmax per (model, image) row of logits [N][B][C] and the combination:
  * probs [N][B][C], mean [B][C] (optional), vote [B], top1 [N][B] (optional). */
 fs_status fs_test_softmax_combine(const float *logits, int32_t N, int32_t B, int32_t C,

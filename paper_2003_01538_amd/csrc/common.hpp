@@ -155,6 +155,9 @@ int fc_pick_split(Prec p, int B, int K, int N, int Z, int num_cus);
 size_t fc_partial_floats(int B, int N, int split, int Z);
 void launch_fc(const FcArgs& a, Prec p, hipStream_t s);  // 1 or 2 launches (split-K reduce)
 int fc_launches(int split);
+// Global average pool g and the layer a that reads it in one launch.
+bool gap_fc_chosen(const PoolArgs& g, const FcArgs& a, Prec p, int num_cus);
+void launch_gap_fc(const PoolArgs& g, const FcArgs& a, Prec p, hipStream_t s);
 
 // ------------------------------------------------------- softmax + combine
 struct SoftmaxArgs {

@@ -25,6 +25,7 @@
 // splits in order (k_fc_reduce).
 #include "common.hpp"
 #include "device.hpp"
+#include "lds_dma.hpp"
 
 #include <algorithm>
 
@@ -282,6 +283,178 @@ __global__ void __launch_bounds__(256) k_fc_reduce(FcArgs a, int out_bf16) {
     (reinterpret_cast<uint16_t*>(a.y) + model * a.y_mstride)[o] = f2bf(v);
   else
     (reinterpret_cast<float*>(a.y) + model * a.y_mstride)[o] = v;
+}
+
+// The global average pool and the classifier after it in one launch, for small
+// batches, whose time is that of launches (6 us each where the work is one):
+// a workgroup pools one image's channels (again in every workgroup of 64
+// features, out of L2; the first also writes them) and its waves take 16
+// features each.  The weights are loaded before the pooling, so the two waits
+// overlap.  Pooling and bf16 products run in the order of k_gap and k_fc (four
+// accumulators stand for that kernel's four waves), so the bits are theirs;
+// fp32 takes plain FMAs, a lane's channels in order and then across the lanes,
+// since its 4-wide matrix steps would be one chain of K / 4.
+//
+// Each launch with events around it, us, two launches against one: 7x7x512 to
+// 1000, three models, bf16 B = 1 6.3 + 6.1 against 8.4; fp32 B = 8 6.1 + 13.0
+// against 13.8.  Bound by three dependent waits on memory and LDS.
+constexpr int GF_K = 512, GF_PL = 16;
+
+// KM: the most channels; NJ: pixels per pixel lane whose loads are in flight
+// together.
+template <int P, int KM, int NJ>
+__global__ void __launch_bounds__(256) k_gap_fc(PoolArgs g, FcArgs a) {
+  using T = typename FcT<P>::T;
+  constexpr int V = P == BF16 ? 8 : 4;
+  __shared__ __attribute__((aligned(16))) float part[GF_PL][GF_K];
+  __shared__ __attribute__((aligned(16))) T gs[GF_K];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n0 = blockIdx.x * 64 + wave * 16, b = blockIdx.y, z = blockIdx.z;
+  const int K = a.K, HW = g.H * g.W;
+  constexpr int ES = sizeof(T);
+  const __amdgpu_buffer_rsrc_t rw = rsrc(reinterpret_cast<const T*>(a.w) + z * a.w_mstride, (uint32_t)(a.N * K * ES));
+  const __amdgpu_buffer_rsrc_t rx =
+      rsrc(reinterpret_cast<const T*>(g.x) + z * g.x_mstride + (int64_t)b * HW * K, (uint32_t)(HW * K * ES));
+
+  // weights (zeros out of range): bf16, MFMA fragments (feature lane & 15, channels 32 s + 8 (lane
+  // >> 4) ..); fp32, channels 4 lane + 256 i .. of every feature
+  constexpr int NL = KM > 256 ? 2 : 1;  // fp32: loads per feature
+  constexpr int NW = P == BF16 ? KM / 32 : 16 * NL;
+  uint4 wv[NW];
+#pragma unroll
+  for (int s = 0; s < NW; ++s) {
+    const int n = n0 + (P == BF16 ? lane & 15 : s / NL);
+    const int k = P == BF16 ? s * 32 + (lane >> 4) * 8 : s % NL * 256 + lane * 4;
+    wv[s] = __builtin_bit_cast(
+        uint4, __builtin_amdgcn_raw_buffer_load_b128(rw, n < a.N && k < K ? (uint32_t)((n * K + k) * ES) : OOB, 0, 0));
+  }
+
+  // all of a thread's loads of 16 NJ pixels at once: one wait on memory, not one per vector
+  constexpr int NG = KM / V / 16;
+  const int pl = tid / 16, cl = tid % 16;
+  float s[NG][V];
+#pragma unroll
+  for (int i = 0; i < NG; ++i)
+#pragma unroll
+    for (int e = 0; e < V; ++e) s[i][e] = 0.f;
+  for (int p0 = pl; p0 < HW; p0 += NJ * GF_PL) {
+    uint4 q[NG][NJ];
+#pragma unroll
+    for (int i = 0; i < NG; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int p = p0 + j * GF_PL, c = (cl + i * 16) * V;
+        q[i][j] = __builtin_bit_cast(
+            uint4, __builtin_amdgcn_raw_buffer_load_b128(rx, p < HW && c < K ? (uint32_t)((p * K + c) * ES) : OOB, 0, 0));
+      }
+#pragma unroll
+    for (int i = 0; i < NG; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        float v[V];
+        if constexpr (P == BF16) {
+          bf8_to_f8(q[i][j], v);
+        } else {
+          v[0] = __uint_as_float(q[i][j].x); v[1] = __uint_as_float(q[i][j].y);
+          v[2] = __uint_as_float(q[i][j].z); v[3] = __uint_as_float(q[i][j].w);
+        }
+#pragma unroll
+        for (int e = 0; e < V; ++e) s[i][e] += v[e];
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < NG; ++i)
+#pragma unroll
+    for (int e = 0; e < V; ++e) part[pl][(cl + i * 16) * V + e] = s[i][e];
+  __syncthreads();
+  for (int c = tid; c < GF_K; c += 256) {
+    float t = 0.f;
+    if (c < K) {
+      t = part[0][c];
+#pragma unroll
+      for (int q = 1; q < GF_PL; ++q) t += part[q][c];
+      t = t / (float)HW;
+    }
+    T r;
+    if constexpr (P == BF16) r = f2bf(t);
+    else r = t;
+    gs[c] = r;  // zeros past K
+    if (blockIdx.x == 0 && c < K) (reinterpret_cast<T*>(g.y) + z * g.y_mstride)[(int64_t)b * K + c] = r;
+  }
+  __syncthreads();
+
+  const float* bias = a.bias + z * a.b_mstride;
+  auto put = [&](int n, float v) {
+    v += bias[n];
+    if (a.relu) v = v > 0.f ? v : 0.f;
+    const int64_t o = (int64_t)b * a.N + n;
+    if (a.out_f32 || P == F32)
+      (reinterpret_cast<float*>(a.y) + z * a.y_mstride)[o] = v;
+    else
+      (reinterpret_cast<uint16_t*>(a.y) + z * a.y_mstride)[o] = f2bf(v);
+  };
+  if constexpr (P == BF16) {
+    floatx4 acc[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NW; ++s) {  // every column of the batch operand is this image
+      const bf16x8 xf = *reinterpret_cast<const bf16x8*>(gs + s * 32 + (lane >> 4) * 8);
+      acc[s & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv[s]), xf, acc[s & 3], 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 1; u < 4; ++u) acc[0] += acc[u];
+    if ((lane & 15) == 0)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int n = n0 + (lane >> 4) * 4 + r;
+        if (n < a.N) put(n, acc[0][r]);
+      }
+  } else {
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      v[i] = 0.f;
+#pragma unroll
+      for (int l = 0; l < NL; ++l) {
+        const floatx4 p = __builtin_bit_cast(floatx4, wv[NL * i + l]);
+        const floatx4 q = *reinterpret_cast<const floatx4*>(gs + l * 256 + lane * 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[i] = fmaf(p[e], q[e], v[i]);
+      }
+    }
+    // sum over the lanes, halving the features a lane holds at each step
+#pragma unroll
+    for (int h = 8; h >= 1; h /= 2) {
+      const bool up = lane & (4 * h);
+#pragma unroll
+      for (int i = 0; i < h; ++i) {
+        const float keep = up ? v[i + h] : v[i], send = up ? v[i] : v[i + h];
+        v[i] = keep + __shfl_xor(send, 4 * h, 64);
+      }
+    }
+    v[0] += __shfl_xor(v[0], 2, 64);
+    v[0] += __shfl_xor(v[0], 1, 64);
+    const int n = n0 + (lane >> 2);
+    if ((lane & 3) == 0 && n < a.N) put(n, v[0]);
+  }
+}
+
+// Whether pool g and layer a, which reads it, run in one launch: as long as
+// the repeated pooling (every workgroup of 64 features) stays one round of the
+// chip, two workgroups a CU.
+bool gap_fc_chosen(const PoolArgs& g, const FcArgs& a, Prec p, int num_cus) {
+  return a.K == g.C && a.K <= GF_K && a.K % (p == BF16 ? 8 : 4) == 0 && (int64_t)g.H * g.W * g.C <= 64 * GF_K &&
+         a.B <= 65535 && a.Z <= 65535 && (int64_t)a.N * a.K * 4 < (int64_t(1) << 31) && (int64_t)((a.N + 63) / 64) * a.B * a.Z <= 2 * num_cus;
+}
+
+void launch_gap_fc(const PoolArgs& g, const FcArgs& a, Prec p, hipStream_t s) {
+  const dim3 grid((a.N + 63) / 64, a.B, a.Z);
+  // few channels: one vector a lane and sixteen pixels in flight instead of 512 channels and four
+  if (p == BF16 && a.K <= 128) hipLaunchKernelGGL((k_gap_fc<BF16, 128, 16>), grid, dim3(256), 0, s, g, a);
+  else if (p == BF16) hipLaunchKernelGGL((k_gap_fc<BF16, GF_K, 4>), grid, dim3(256), 0, s, g, a);
+  else if (a.K <= 64) hipLaunchKernelGGL((k_gap_fc<F32, 64, 16>), grid, dim3(256), 0, s, g, a);
+  else hipLaunchKernelGGL((k_gap_fc<F32, GF_K, 4>), grid, dim3(256), 0, s, g, a);
 }
 
 static int fc_fb(int B) { return B > 32 ? 4 : (B > 16 ? 2 : 1); }

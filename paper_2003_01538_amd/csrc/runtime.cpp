@@ -939,6 +939,41 @@ bool pair_args(fs_ensemble* e, Group& g, const LayerPlan& P, int li, int B, cons
   return conv_pair_chosen(a, *d, e->num_cus);
 }
 
+PoolArgs pool_args(const Group& g, const LayerPlan& P, int B, const void* x, int64_t x_ms, void* y, int64_t y_ms) {
+  PoolArgs a{};
+  a.x = x; a.x_mstride = x_ms; a.y = y; a.y_mstride = y_ms;
+  a.B = B; a.H = P.in.H; a.W = P.in.W; a.C = P.in.C;
+  a.Ho = P.out.H; a.Wo = P.out.W; a.k = P.kh; a.stride = P.stride; a.pad = P.pad; a.Z = g.Z;
+  return a;
+}
+
+FcArgs fc_args(fs_ensemble* e, Group& g, const LayerPlan& P, int B, const void* x, int64_t x_ms, void* y,
+               int64_t y_ms) {
+  char* arena = static_cast<char*>(e->arena->p);
+  FcArgs a{};
+  a.x = x; a.x_mstride = x_ms;
+  a.w = arena + P.w_off; a.w_mstride = P.w_melems;
+  a.bias = reinterpret_cast<const float*>(arena + P.b_off); a.b_mstride = P.b_melems;
+  a.y = y; a.y_mstride = y_ms;
+  a.partial = static_cast<float*>(g.fc_partial.p ? g.fc_partial.p : e->partial.p);
+  a.B = B; a.K = P.K; a.N = P.out.C; a.relu = P.relu; a.out_f32 = P.last ? 1 : 0;
+  a.Z = g.Z;
+  a.split = fc_pick_split(e->prec, B, a.K, a.N, g.Z, e->num_cus);
+  return a;
+}
+
+// Whether layer li, a global average pool, runs in one launch with the
+// classifier after it at this batch size (the last layer only: its logits
+// share no slot with what the pool reads).
+bool gap_fc(fs_ensemble* e, Group& g, int li, int B) {
+  const LayerPlan& P = g.layers[li];
+  if (P.op != FS_OP_GAP || P.fused_away || li + 1 >= (int)g.layers.size()) return false;
+  const LayerPlan& N = g.layers[li + 1];
+  return N.op == FS_OP_FC && N.last && N.src == li &&
+         gap_fc_chosen(pool_args(g, P, B, nullptr, 0, nullptr, 0), fc_args(e, g, N, B, nullptr, 0, nullptr, 0),
+                       e->prec, e->num_cus);
+}
+
 int batch_bucket(int B, int max_batch) {
   int b = 1;
   while (b < B) b <<= 1;
@@ -1116,7 +1151,6 @@ void run_pass(fs_ensemble* e, const uint8_t* d_pixels, const ImageDesc* d_desc, 
     }
   }
 
-  char* arena = static_cast<char*>(e->arena->p);
   const std::vector<std::vector<int>>& tiles = tiles_for(e, B, s);
   const hipStream_t s_main = s;
   const bool multi = e->fork != nullptr;
@@ -1205,10 +1239,20 @@ void run_pass(fs_ensemble* e, const uint8_t* d_pixels, const ImageDesc* d_desc, 
         case FS_OP_MAXPOOL:
         case FS_OP_GAP: {
           if (P.fused_away) break;
-          PoolArgs a{};
-          a.x = x; a.x_mstride = x_ms; a.y = y; a.y_mstride = y_ms;
-          a.B = B; a.H = P.in.H; a.W = P.in.W; a.C = P.in.C;
-          a.Ho = P.out.H; a.Wo = P.out.W; a.k = P.kh; a.stride = P.stride; a.pad = P.pad; a.Z = g.Z;
+          const PoolArgs a = pool_args(g, P, B, x, x_ms, y, y_ms);
+          if (gap_fc(e, g, (int)li, B)) {
+            const LayerPlan& N = g.layers[li + 1];
+            const FcArgs f = fc_args(e, g, N, B, y, y_ms, logits + (int64_t)g.first * B * e->C, (int64_t)B * e->C);
+            launch.M = B; launch.N = f.N; launch.K = f.K;
+            launch.kernel = "gap_fc";
+            launch(K_FC, 2.0 * B * f.N * (double)f.K * g.Z,
+                   (((double)f.N * f.K + (double)B * P.in.elems() + (double)B * f.K) * esz + (double)B * f.N * 4) * g.Z, 1,
+                   [&] { launch_gap_fc(a, f, p, s); });
+            dbg_capture(e, g, (int)li, y, y_ms, P.out.elems(), esz, B, s);
+            dbg_capture(e, g, (int)li + 1, f.y, f.y_mstride, f.N, 4, B, s);
+            skip_next = true;
+            break;
+          }
           const double bytes = ((double)B * P.in.elems() + (double)B * P.out.elems()) * esz * g.Z;
           if (P.op == FS_OP_MAXPOOL)
             launch(K_MAXPOOL, 0.0, bytes, 1, [&] { launch_maxpool(a, p, s); });
@@ -1218,15 +1262,7 @@ void run_pass(fs_ensemble* e, const uint8_t* d_pixels, const ImageDesc* d_desc, 
           break;
         }
         case FS_OP_FC: {
-          FcArgs a{};
-          a.x = x; a.x_mstride = x_ms;
-          a.w = arena + P.w_off; a.w_mstride = P.w_melems;
-          a.bias = reinterpret_cast<const float*>(arena + P.b_off); a.b_mstride = P.b_melems;
-          a.y = y; a.y_mstride = y_ms;
-          a.partial = static_cast<float*>(g.fc_partial.p ? g.fc_partial.p : e->partial.p);
-          a.B = B; a.K = P.K; a.N = P.out.C; a.relu = P.relu; a.out_f32 = P.last ? 1 : 0;
-          a.Z = g.Z;
-          a.split = fc_pick_split(p, B, a.K, a.N, g.Z, e->num_cus);
+          const FcArgs a = fc_args(e, g, P, B, x, x_ms, y, y_ms);
           launch.M = B; launch.N = a.N; launch.K = a.K;
           launch.kernel = a.split > 1 ? "fc_splitk" : "fc";
           const double flops = 2.0 * B * a.N * (double)a.K * g.Z;
@@ -1273,7 +1309,10 @@ int launches_per_pass(fs_ensemble* e) {
     for (size_t li = 0; li < g.layers.size(); ++li) {
       LayerPlan& P = g.layers[li];
       if (skip_next) { skip_next = false; continue; }
-      if (P.op == FS_OP_FC) {
+      if (gap_fc(e, g, (int)li, e->max_batch)) {
+        n += 1;
+        skip_next = true;
+      } else if (P.op == FS_OP_FC) {
         n += fc_launches(fc_pick_split(e->prec, e->max_batch, P.K, P.out.C, g.Z, e->num_cus));
       } else if (P.op == FS_OP_CONV && P.proj_into < 0) {
         const ConvArgs a = conv_args(e, g, P, e->max_batch, nullptr, 0);
@@ -2274,6 +2313,37 @@ fs_status fs_test_gap(const float* in, int32_t B, int32_t H, int32_t W, int32_t 
     HIPCHK(hipGetLastError());
     HIPCHK(hipDeviceSynchronize());
     download_as(out, dy, (int64_t)B * C, p);
+  });
+}
+
+fs_status fs_test_gap_fc(const float* in, int32_t B, int32_t H, int32_t W, int32_t K, const float* w,
+                         const float* bias, int32_t N, int32_t relu, int32_t precision, float* pooled, float* out,
+                         int32_t device) {
+  return guarded(nullptr, [&] {
+    Prec p = prec_of(precision);
+    if (!in || !w || !bias || !pooled || !out || B < 1 || H < 1 || W < 1 || K < 1 || N < 1)
+      fail(FS_ERR_INVALID, "bad gap_fc arguments");
+    if (K % (p == BF16 ? 8 : 4)) fail(FS_ERR_UNSUPPORTED, "K must be a multiple of the vector width");
+    set_device(device);
+    TmpDev t;
+    PoolArgs g{};
+    g.x = upload_as(t, in, (int64_t)B * H * W * K, p);
+    g.y = t.alloc((size_t)B * K * es(p));
+    g.B = B; g.H = H; g.W = W; g.C = K; g.Ho = 1; g.Wo = 1; g.Z = 1;
+    FcArgs a{};
+    a.x = g.y;
+    a.w = upload_as(t, w, (int64_t)N * K, p);
+    void* db = t.alloc(N * 4);
+    HIPCHK(hipMemcpy(db, bias, N * 4, hipMemcpyHostToDevice));
+    a.bias = static_cast<const float*>(db);
+    a.y = t.alloc((size_t)B * N * 4);
+    a.B = B; a.K = K; a.N = N; a.relu = relu ? 1 : 0; a.out_f32 = 1; a.Z = 1; a.split = 1;
+    if (!gap_fc_chosen(g, a, p, num_cus_of(device))) fail(FS_ERR_UNSUPPORTED, "not a pool and layer the kernel takes");
+    launch_gap_fc(g, a, p, nullptr);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipDeviceSynchronize());
+    download_as(pooled, g.y, (int64_t)B * K, p);
+    download_as(out, a.y, (int64_t)B * N, F32);
   });
 }
 

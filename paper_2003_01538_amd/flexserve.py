@@ -132,6 +132,8 @@ SIGNATURES = [
     ("fs_test_gap", ctypes.c_int, [_fp] + [ctypes.c_int32] * 5 + [_fp, ctypes.c_int32]),
     ("fs_test_fc", ctypes.c_int, [_fp, ctypes.c_int32, ctypes.c_int32, _fp, _fp, ctypes.c_int32,
                                   ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, _fp, ctypes.c_int32]),
+    ("fs_test_gap_fc", ctypes.c_int, [_fp] + [ctypes.c_int32] * 4 + [_fp, _fp] + [ctypes.c_int32] * 3 +
+                                     [_fp, _fp, ctypes.c_int32]),
     ("fs_test_softmax_combine", ctypes.c_int, [_fp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                                                _fp, _fp, _i32p, _i32p, ctypes.c_int32]),
     ("fs_test_softmax_combine_policy", ctypes.c_int, [_fp] + [ctypes.c_int32] * 6 +
@@ -482,6 +484,18 @@ def fs_test_fc(x, w, bias, relu, precision, out_storage=False, device=0):
     _check(load().fs_test_fc(_f(x), B, K, _f(w), _f(b), N, int(relu), precision, int(out_storage),
                              _f(out), device))
     return out
+
+
+def fs_test_gap_fc(x, w, bias, relu, precision, device=0):
+    x = np.ascontiguousarray(x, np.float32)
+    w = np.ascontiguousarray(w, np.float32)
+    b = np.ascontiguousarray(bias, np.float32)
+    B, H, W, K = x.shape
+    N = w.shape[0]
+    pooled, out = np.zeros((B, K), np.float32), np.zeros((B, N), np.float32)
+    _check(load().fs_test_gap_fc(_f(x), B, H, W, K, _f(w), _f(b), N, int(relu), precision, _f(pooled), _f(out),
+                                 device))
+    return pooled, out
 
 
 def fs_test_softmax_combine(logits, device=0):
