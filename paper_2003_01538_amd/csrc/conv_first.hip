@@ -17,7 +17,8 @@
 // filter does not reach): 24 MFMAs for 128 conv pixels, as many as with
 // operands gathered per conv pixel, for a fifth of the loads.  The max over
 // the window is then a max over accumulators.  It commutes with the rounding
-// (both are monotone), so the result is that of the two layers.
+// (both are monotone), so the result is that of the two layers up to the order
+// of the 36 terms of a sum.
 //
 // VGG-11's first layer, 32 images of 224 x 224: 31 us (2 TB/s) against 124 +
 // 43 us in two launches, each measured alone with events around it.  Bound
@@ -92,6 +93,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_first_pool(ConvArgs a, int wave
       v[r][1] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(rx, ro + c1, 0, 0));
     }
   };
+  const uint32_t low = fq ? 0u : ~0u;  // columns 0 and 1 of the patch
   v2u cur[4][2], nxt[4][2];
   load(cur);
   for (int t0 = wave * 32; t0 < total; t0 += step) {
@@ -107,10 +109,14 @@ __global__ void __launch_bounds__(256, 2) k_conv_first_pool(ConvArgs a, int wave
     }
     if (py >= Hp) py -= Hp;
     load(nxt);  // past the last window: nothing is read
-    bf16x8 f[4];
+    // the column that the pixels of shift dx do not read is cleared: it meets
+    // a zero weight, but zero times a pixel that is not finite is not zero
+    bf16x8 f[2][4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      f[r] = __builtin_bit_cast(bf16x8, v4u{cur[r][0][0], cur[r][0][1], cur[r][1][0], cur[r][1][1]});
+    for (int r = 0; r < 4; ++r) {
+      f[0][r] = __builtin_bit_cast(bf16x8, v4u{cur[r][0][0], cur[r][0][1], cur[r][1][0] & low, cur[r][1][1] & low});
+      f[1][r] = __builtin_bit_cast(bf16x8, v4u{cur[r][0][0] & ~low, cur[r][0][1] & ~low, cur[r][1][0], cur[r][1][1]});
+    }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       floatx16 acc[2][2];
@@ -122,7 +128,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_first_pool(ConvArgs a, int wave
           for (int e = 0; e < 16; ++e) acc[dy][dx][e] = 0.f;
 #pragma unroll
           for (int ky = 0; ky < 3; ++ky)
-            acc[dy][dx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ky][dx][j], f[dy + ky], acc[dy][dx], 0, 0, 0);
+            acc[dy][dx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ky][dx][j], f[dx][dy + ky], acc[dy][dx], 0, 0, 0);
         }
       float v[16];
 #pragma unroll

@@ -30,6 +30,26 @@ def test_first_conv_maxpool_fused(gpu_lib, B, H, W):
     assert np.array_equal(np.isinf(g), np.isinf(sep)) and not np.isnan(g).any() and np.isinf(g).any()
 
 
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_a_pixel_reaches_only_the_windows_that_read_it(gpu_lib, value):
+    # a pixel beside a window is read by one of its two columns of conv pixels:
+    # the other column's sums stay finite and may be the window's maximum
+    rng = np.random.default_rng(8)
+    B, H, W = 2, 12, 20
+    x = oracle.round_bf16(rng.standard_normal((B, H, W, 3)).astype(np.float32))
+    w = oracle.round_bf16((rng.standard_normal((64, 3, 3, 3)) * np.sqrt(2.0 / 27)).astype(np.float32))
+    b = (rng.standard_normal(64) * 0.1).astype(np.float32)
+    _, ab = oracle.conv2d(x, w, b, 1, 1, 1, None, "bf16", want_abs=True)
+    x[0, 3, 2, 0] = x[0, 8, 7, 1] = x[1, 0, 19, 2] = x[1, 11, 0, 0] = value
+    g = fsb.fs_test_first_pool(x, w, b)
+    sep = fsb.fs_test_maxpool(fsb.fs_test_conv(x, w, b, None, 1, 1, 1, BF16), 2, 2, 0, BF16)
+    inf = np.isinf(sep)
+    assert np.array_equal(np.isinf(g), inf) and not np.isnan(g).any()
+    # the finite outputs as for finite inputs: the pixels' magnitudes are those of `ab` or drop out as a zero
+    z = lambda v: np.where(inf, 0, v).astype(np.float32)
+    assert_bf16_close(z(g), z(sep), oracle.maxpool(ab, 2, 2, 0), what=f"{value}")
+
+
 def test_odd_maps_are_refused(gpu_lib):
     z = lambda *s: np.zeros(s, np.float32)
     for h, w in [(7, 8), (8, 7)]:
