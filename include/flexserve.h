@@ -321,6 +321,16 @@ fs_status fs_test_conv(const float *in, int32_t B, int32_t H, int32_t W, int32_t
                        int32_t kh, int32_t kw, int32_t stride, int32_t pad, int32_t relu,
                        int32_t precision, int32_t tile, float *out, int32_t device);
 
+/* Which kernel runs a convolution layer where nothing is timed: *tile (see
+ * fs_conv_tile_name) and the number of workgroups that split the reduction,
+ * for Z models per launch on a GPU of num_cus CUs.  packed = 0: as in an
+ * ensemble, whose bf16 weights are also kept in fragment order; 1: as in
+ * fs_conv_bf16_device_noalloc (bf16, Z = 1), whose caller has the packed rows
+ * only.  FS_ERR_UNSUPPORTED where no kernel takes the layer.  Needs no GPU. */
+fs_status fs_test_conv_choice(int32_t B, int32_t H, int32_t W, int32_t Cin, int32_t Cout, int32_t kh,
+                              int32_t kw, int32_t stride, int32_t pad, int32_t precision, int32_t Z,
+                              int32_t packed, int32_t num_cus, int32_t *tile, int32_t *split);
+
 /* A widening 1x1 conv and the narrowing 1x1 conv that reads it, bf16, both
  * with ReLU: y = relu(w1 . [in | in2 at stride2] + bias1 + res), out =
  * relu(w2 . y + bias2); in2 (a projection shortcut's input) or res, or

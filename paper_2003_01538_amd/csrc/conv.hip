@@ -306,6 +306,8 @@ static const ConvTile kTilesF32[] = {  // in the order of conv_f32_tile; wgm: gr
     {64, 64, 4, "f32_64x64_v4", 0, 4, 1},
     {32, 32, 4, "f32_32x32_k4_v4", 0, 4, 4},
     {32, 32, 4, "f32_32x32_k8_v4", 0, 8, 8},
+    {64, 32, 4, "f32_64x32_v4", 0, 2, 1},
+    {128, 32, 4, "f32_128x32_v4", 0, 4, 1},
 };
 
 int conv_num_tiles(Prec p) {

@@ -222,32 +222,55 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) k_conv_f32(ConvArgs a) {
       constexpr int s = decltype(sc)::value;
       if (i + s < n_steps) {
         wait_vmcnt<(STAGES - 2) * LPT>();
-        if constexpr (G > 1) wg_barrier();
+        if constexpr (G > 1) {
+          wait_lgkm0();  // this wave's operand reads of the stage that is filled next
+          wg_barrier();
+        }
         issue(ring + (s + STAGES - 1) % STAGES * STAGE);
         compute(sc);
       }
     });
 
   // ---- bias, residual, ReLU.  D[n][m]: lane l holds pixel l % 32 and channels
-  // 8 g + 4 (l / 32) + r: four consecutive ones, one 16-byte store per g
-  const float* __restrict__ bias = a.bias + z * a.b_mstride;
+  // 8 g + 4 (l / 32) + r: four consecutive ones, one 16-byte store per g.  Pieces
+  // outside the layer read zeros and store nothing instead of being skipped, so
+  // that a lane's loads are all in flight together.
   const uint32_t obytes = (uint32_t)((int64_t)a.M * a.Cout * 4);
   const bool has_res = a.res != nullptr;
+  const __amdgpu_buffer_rsrc_t rb = rsrc(a.bias + z * a.b_mstride, (uint32_t)a.Cout * 4u);
   const __amdgpu_buffer_rsrc_t rres =
       has_res ? rsrc(reinterpret_cast<const float*>(a.res) + z * a.res_mstride, obytes) : rsrc(a.y, 0u);
   const __amdgpu_buffer_rsrc_t ry = rsrc(reinterpret_cast<float*>(a.y) + z * a.y_mstride, obytes);
-  auto finish = [&](floatx4 v, int m, int n) {
-    if (m >= a.M || n >= a.Cout) return;
-    const uint32_t o = (uint32_t)(((int64_t)m * a.Cout + n) * 4);
-    v += *reinterpret_cast<const floatx4*>(bias + n);
-    if (has_res) v += __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rres, o, 0, 0));
+  auto load4 = [&](const __amdgpu_buffer_rsrc_t& r, uint32_t o) {
+    return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, o, 0, 0));
+  };
+  auto out_off = [&](int m, int n) {
+    return m < a.M && n < a.Cout ? (uint32_t)(((int64_t)m * a.Cout + n) * 4) : OOB;
+  };
+  auto finish = [&](floatx4 v, floatx4 b, floatx4 r, uint32_t o) {
+    v += b;
+    if (has_res) v += r;
     if (a.relu)
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), ry, o, 0, 0);
   };
-  wait_vmcnt<0>();  // the out-of-range loads past the last tile land before the LDS is reused, or the workgroup leaves
   if constexpr (KS == 1) {
+    uint32_t o[FM][FN][4];
+    floatx4 bv[FN][4], rv[FM][FN][4];
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int gg = 0; gg < 4; ++gg) {
+        const int n = n0 + (wn * FN + j) * 32 + 8 * gg + 4 * fq;
+        bv[j][gg] = load4(rb, (uint32_t)n * 4u);
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+          o[i][j][gg] = out_off(m0 + (wm * FM + i) * 32 + fr, n);
+          rv[i][j][gg] = has_res ? load4(rres, o[i][j][gg]) : floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+    wait_vmcnt<0>();  // also the out-of-range loads past the last tile, before the workgroup leaves its LDS
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -255,9 +278,10 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) k_conv_f32(ConvArgs a) {
 #pragma unroll
         for (int gg = 0; gg < 4; ++gg)
           finish(floatx4{acc[i][j][gg * 4], acc[i][j][gg * 4 + 1], acc[i][j][gg * 4 + 2], acc[i][j][gg * 4 + 3]},
-                 m0 + (wm * FM + i) * 32 + fr, n0 + (wn * FN + j) * 32 + 8 * gg + 4 * fq);
+                 bv[j][gg], rv[i][j][gg], o[i][j][gg]);
   } else {
     static_assert(KS == 1 || G == 1, "split groups are single waves");
+    wait_vmcnt<0>();  // the out-of-range loads past the last tile land before the LDS is reused
     wg_barrier();
     constexpr int WAVE = FM * FN * 4 * F32_BLK;
 #pragma unroll
@@ -273,11 +297,14 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) k_conv_f32(ConvArgs a) {
     // one item = one pixel x 4 channels; eight consecutive items are a pixel's 32 channels
     for (int it = tid; it < FM * FN * 256; it += 64 * NW) {
       const int blk = it >> 8, px = (it >> 3) & 31, c4 = it & 7;
+      const int n = n0 + (blk % FN) * 32 + c4 * 4;
+      const uint32_t o = out_off(m0 + (blk / FN) * 32 + px, n);
+      const floatx4 bv = load4(rb, (uint32_t)n * 4u), rv = has_res ? load4(rres, o) : floatx4{0.f, 0.f, 0.f, 0.f};
       const char* src = smem + (blk * 4 + (c4 >> 1)) * F32_BLK + ((c4 & 1) * 32 + px) * 16;
       floatx4 v = *reinterpret_cast<const floatx4*>(src);
 #pragma unroll
       for (int k = 1; k < KS; ++k) v += *reinterpret_cast<const floatx4*>(src + k * WAVE);
-      finish(v, m0 + (blk / FN) * 32 + px, n0 + (blk % FN) * 32 + c4 * 4);
+      finish(v, bv, rv, o);
     }
   }
 }
@@ -303,30 +330,51 @@ void launch_conv_f32(const ConvArgs& a, int bm, int bn, int ks, hipStream_t s) {
                          0, s, a);                                                                                 \
     return;                                                                                                        \
   }
-  FS_F32(1, 1, 2, 2, 1, 3) FS_F32(1, 1, 1, 1, 4, 2) FS_F32(1, 1, 1, 1, 8, 2)
+  FS_F32(1, 1, 2, 2, 1, 3) FS_F32(1, 1, 1, 1, 4, 2) FS_F32(1, 1, 1, 1, 8, 2) FS_F32(1, 1, 2, 1, 1, 2) FS_F32(1, 1, 4, 1, 1, 2)
 #undef FS_F32
 }
 
-// The tile of a layer: 64x64 (0), or 32x32 with the reduction over four (1) or
-// eight waves (2).  Estimated time (us) of the workgroups that share the
-// busiest CU, from back-to-back launches of every tile on 14 layer shapes at 1
-// to 32 images and one or three models: a K-tile of a wave takes 0.54 us
-// alone on its SIMD and 0.45 to 0.47 among others.  Measured, three models at
-// eight images (us, 64x64 / 32x32 over four / over eight waves): 56x56x64
-// 53.7 / 78 / 114, 28x28x128 58.8 / 61.6 / 78, 14x14x256 77 / 56.2 / 60.5,
-// 7x7x512 85.6 / 62.8 / 62.3; one image, 7x7x512: 82.6 / 25.4 / 22.3.
-// Shape and batch decide alone (the 256 CUs are the chip's), so a result's
-// bits never depend on timing.
+// The tile of a layer: 64x64 (0), 32x32 with the reduction over four (1) or
+// eight waves (2), or, for layers whose channels would leave 64 columns half
+// empty, 64x32 (3) and 128x32 (4) with the waves along the pixels.  Time in us of
+// a layer on each: a + b q + (c q + d) ceil(n) + f n, with q K-tiles per wave and
+// n workgroups per CU (at least one); coefficients fitted (non-negative, least
+// squares of the relative error, 3 to 7 % rms) to back-to-back launches of every
+// tile on 283 layers: 3 to 256 channels in, 8 to 256 out, 1x1 to 5x5, maps of 4 to
+// 56, B = 1 to 64, one to three models.  The tile it names is 0.6 % slower than the
+// fastest of the five on average and 9 % at most.  Without the narrow tiles
+// layers of few channels lost up to half their speed to empty columns: 3x3,
+// 3 -> 16 on 32x32, B = 64, three models, 24.7 us on 64x64 against 14.7 on 128x32;
+// 1x1, 64 -> 24 on 32x32, B = 64, two models, 17.7 against 11.0.  With channels to
+// fill them wider tiles win: 56x56x64, B = 8, three models, 53.7 on 64x64 against
+// 78 on 32x32 over four waves; 14x14x256 77 against 56.2; one image, 7x7x512 82.6
+// against 25.4 over four and 22.3 over eight.  Shape and batch decide alone (the
+// 256 CUs are the chip's), so a result's bits never depend on timing.
+struct F32Cost {
+  int bm, bn, ks;
+  double a, b, c, d, f;
+};
+static const F32Cost kF32Cost[] = {
+    {64, 64, 1, 2.30, 0.13, 0.45, 1.15, 0.},      {32, 32, 4, 1.97, 0.12, 0.51, 0.48, 0.71},
+    {32, 32, 8, 1.10, 0.01, 1.00, 2.57, 0.05},    {64, 32, 1, 2.76, 0.37, 0.24, 0.57, 0.},
+    {128, 32, 1, 2.26, 0.21, 0.45, 1.10, 0.},
+};
+
 int conv_f32_tile(const ConvArgs& a) {
-  const double nk = (a.K + F32_BK - 1) / F32_BK;
-  auto per_cu = [&](int b) {
-    return std::ceil((double)((a.M + b - 1) / b) * ((a.Cout + b - 1) / b) * a.Z / 256.0);
-  };
-  const double n64 = per_cu(64), n32 = per_cu(32), t4 = std::ceil(nk / 4), t8 = std::ceil(nk / 8);
-  const double e[3] = {n64 <= 1 ? nk * 0.54 : 1.1 * n64 * nk * 0.47,
-                       n32 <= 1 ? t4 * 0.54 : 1.1 * n32 * (t4 * 0.45 + 1.3),
-                       n32 <= 1 ? t8 * 0.9 + 1.0 : 1.1 * n32 * (t8 * 0.9 + 1.5)};
-  return (int)(std::min_element(e, e + 3) - e);
+  const int nk = (a.K + F32_BK - 1) / F32_BK;
+  int best = 0;
+  double best_us = 1e300;
+  for (int i = 0; i < (int)(sizeof(kF32Cost) / sizeof(F32Cost)); ++i) {
+    const F32Cost& t = kF32Cost[i];
+    const double tiles = (double)((a.M + t.bm - 1) / t.bm) * ((a.Cout + t.bn - 1) / t.bn) * a.Z;
+    const double n = std::max(1.0, tiles / 256), q = (nk + t.ks - 1) / t.ks;
+    const double us = t.a + t.b * q + (t.c * q + t.d) * std::ceil(n) + t.f * n;
+    if (us < best_us) {
+      best_us = us;
+      best = i;
+    }
+  }
+  return best;
 }
 
 }  // namespace fs

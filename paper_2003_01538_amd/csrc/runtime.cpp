@@ -2199,6 +2199,28 @@ fs_status fs_test_conv(const float* in, int32_t B, int32_t H, int32_t W, int32_t
   });
 }
 
+fs_status fs_test_conv_choice(int32_t B, int32_t H, int32_t W, int32_t Cin, int32_t Cout, int32_t kh, int32_t kw,
+                              int32_t stride, int32_t pad, int32_t precision, int32_t Z, int32_t packed,
+                              int32_t num_cus, int32_t* tile, int32_t* split) {
+  return guarded(nullptr, [&] {
+    const Prec p = prec_of(precision);
+    if (!tile || !split || B < 1 || H < 1 || W < 1 || Cin < 1 || Cout < 1 || kh < 1 || kw < 1 || stride < 1 || pad < 0 ||
+        Z < 1 || num_cus < 1)
+      fail(FS_ERR_INVALID, "bad conv arguments");
+    if (H + 2 * pad < kh || W + 2 * pad < kw) fail(FS_ERR_INVALID, "conv output would be empty");
+    ConvArgs a{};
+    a.B = B; a.H = H; a.W = W; a.Cin = Cin == 3 ? 4 : Cin; a.Cout = Cout;
+    a.Ho = (H + 2 * pad - kh) / stride + 1; a.Wo = (W + 2 * pad - kw) / stride + 1;
+    a.kh = kh; a.kw = kw; a.stride = stride; a.pad = pad;
+    a.K = kh * kw * a.Cin; a.Kp = (int)round_up(a.K, CONV_KPAD); a.M = B * a.Ho * a.Wo; a.Z = Z;
+    if (!packed && conv_frag_wanted(p, Cout, a.Kp)) a.wf = &a;  // only asked whether it is there
+    a.split = conv_split(p, a, num_cus);
+    *tile = conv_pick_tile(p, a, num_cus);
+    if (*tile < 0 || !conv_tile_ok(p, *tile, a)) fail(FS_ERR_UNSUPPORTED, "no conv kernel takes this shape");
+    *split = conv_tile_direct(conv_tile(p, *tile)) ? a.split : 1;
+  });
+}
+
 fs_status fs_test_conv_pair(const float* in, int32_t B, int32_t H, int32_t W, int32_t Cin, const float* in2,
                             int32_t H2, int32_t W2, int32_t Cin2, int32_t stride2, const float* w1,
                             const float* bias1, const float* res, int32_t N1, const float* w2, const float* bias2,

@@ -1,0 +1,29 @@
+"""Which kernel a convolution layer gets where nothing is timed: layers that
+were measured, on both sides of each rule's line.  The rules see shapes only,
+so this needs no GPU."""
+import re
+
+import pytest
+
+from paper_2003_01538_amd import flexserve as fsb
+
+
+def tile_size(name):
+    return tuple(int(v) for v in re.search(r"_(\d+)x(\d+)", name).groups())
+
+
+@pytest.mark.parametrize("cin,cout,k,hw,B,Z", [
+    (3, 16, 3, 32, 8, 3), (3, 16, 3, 32, 64, 1), (3, 16, 3, 32, 64, 3),   # a small net's first layer
+    (64, 24, 1, 32, 64, 2), (32, 8, 1, 56, 64, 2), (3, 32, 3, 56, 8, 3), (32, 96, 3, 56, 4, 2),
+])
+def test_fp32_layers_do_not_run_on_half_empty_tiles(cin, cout, k, hw, B, Z):
+    name, split = fsb.fs_test_conv_choice(B, hw, hw, cin, cout, k, 1, k // 2, fsb.FS_F32, Z)
+    bm, bn = tile_size(name)
+    assert bn == 32 and split == 1, name
+
+
+@pytest.mark.parametrize("cin,cout,hw,B,Z,want", [
+    (64, 64, 56, 8, 3, "f32_64x64_v4"), (256, 256, 14, 8, 3, "f32_32x32_k4_v4"), (512, 512, 7, 1, 3, "f32_32x32_k8_v4"),
+])
+def test_fp32_layers_whose_channels_fill_the_tile(cin, cout, hw, B, Z, want):
+    assert fsb.fs_test_conv_choice(B, hw, hw, cin, cout, 3, 1, 1, fsb.FS_F32, Z) == (want, 1)
