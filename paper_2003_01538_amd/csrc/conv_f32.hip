@@ -51,8 +51,13 @@ __device__ __forceinline__ void load16_lds(const void* base, uint32_t bytes, cha
 // therefore take their time from them, whichever wave issues them: with the tap
 // worked out per lane and K-tile (75 vector instructions to 16 MFMAs) the
 // matrix rate stopped at 100 TFLOP/s on every tile shape.
-template <int FM, int FN, int WM, int WN, int KS, int STAGES, bool UNI>
+//
+// WIDE: a filter of 2^24 values, or one that spans 2^23 pixels, which the 24-bit
+// products and fdiv_small of the general form do not cover.
+enum { F32_GEN, F32_UNI, F32_WIDE };
+template <int FM, int FN, int WM, int WN, int KS, int STAGES, int FORM>
 __global__ void __launch_bounds__(64 * WM * WN * KS) k_conv_f32(ConvArgs a) {
+  constexpr bool UNI = FORM == F32_UNI;
   constexpr int G = WM * WN, NW = G * KS;
   constexpr int BM = 32 * FM * WM, BN = 32 * FN * WN;
   constexpr int AP = BM / 8 / G, BP = BN / 8 / G, LPT = AP + BP;  // load instructions per wave and K-tile
@@ -143,11 +148,20 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) k_conv_f32(ConvArgs a) {
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
         const int gch = u * 8 + ((lane & 7) ^ lr ^ p);
-        const int tap = fdiv_small(gch, inv_cpt);
-        const int ty = fdiv_small(tap, inv_kw), tx = tap - __mul24(ty, a.kw);
+        int tap, ty, tx;
+        if constexpr (FORM == F32_WIDE) {
+          tap = gch / cpt;
+          ty = tap / a.kw;
+          tx = tap - ty * a.kw;
+          dof[p] = (int)(((uint32_t)ty * a.W + tx) * a.Cin + ((gch - tap * cpt) << 2));
+        } else {
+          tap = fdiv_small(gch, inv_cpt);
+          ty = fdiv_small(tap, inv_kw);
+          tx = tap - __mul24(ty, a.kw);
+          dof[p] = __mul24(__mul24(ty, a.W) + tx, a.Cin) + ((gch - __mul24(tap, cpt)) << 2);
+        }
         dy[p] = tap < taps ? ty : -(1 << 28);  // past the filter: outside the image
         dx[p] = tx;
-        dof[p] = __mul24(__mul24(ty, a.W) + tx, a.Cin) + ((gch - __mul24(tap, cpt)) << 2);
       }
 #pragma unroll
       for (int i = 0; i < AP; ++i) {
@@ -232,12 +246,13 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) k_conv_f32(ConvArgs a) {
     });
 
   // ---- bias, residual, ReLU.  D[n][m]: lane l holds pixel l % 32 and channels
-  // 8 g + 4 (l / 32) + r: four consecutive ones, one 16-byte store per g.  Pieces
-  // outside the layer read zeros and store nothing instead of being skipped, so
-  // that a lane's loads are all in flight together.
+  // 8 g + 4 (l / 32) + r: four consecutive ones, one 16-byte store per g.  With
+  // one group, pieces outside the layer read zeros and store nothing instead of
+  // being skipped, so that a lane's loads are all in flight together.
   const uint32_t obytes = (uint32_t)((int64_t)a.M * a.Cout * 4);
   const bool has_res = a.res != nullptr;
-  const __amdgpu_buffer_rsrc_t rb = rsrc(a.bias + z * a.b_mstride, (uint32_t)a.Cout * 4u);
+  const float* __restrict__ bias = a.bias + z * a.b_mstride;
+  const __amdgpu_buffer_rsrc_t rb = rsrc(bias, (uint32_t)a.Cout * 4u);
   const __amdgpu_buffer_rsrc_t rres =
       has_res ? rsrc(reinterpret_cast<const float*>(a.res) + z * a.res_mstride, obytes) : rsrc(a.y, 0u);
   const __amdgpu_buffer_rsrc_t ry = rsrc(reinterpret_cast<float*>(a.y) + z * a.y_mstride, obytes);
@@ -297,14 +312,14 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) k_conv_f32(ConvArgs a) {
     // one item = one pixel x 4 channels; eight consecutive items are a pixel's 32 channels
     for (int it = tid; it < FM * FN * 256; it += 64 * NW) {
       const int blk = it >> 8, px = (it >> 3) & 31, c4 = it & 7;
-      const int n = n0 + (blk % FN) * 32 + c4 * 4;
-      const uint32_t o = out_off(m0 + (blk / FN) * 32 + px, n);
-      const floatx4 bv = load4(rb, (uint32_t)n * 4u), rv = has_res ? load4(rres, o) : floatx4{0.f, 0.f, 0.f, 0.f};
+      const int m = m0 + (blk / FN) * 32 + px, n = n0 + (blk % FN) * 32 + c4 * 4;
+      if (m >= a.M || n >= a.Cout) continue;
       const char* src = smem + (blk * 4 + (c4 >> 1)) * F32_BLK + ((c4 & 1) * 32 + px) * 16;
       floatx4 v = *reinterpret_cast<const floatx4*>(src);
 #pragma unroll
       for (int k = 1; k < KS; ++k) v += *reinterpret_cast<const floatx4*>(src + k * WAVE);
-      finish(v, bv, rv, o);
+      const uint32_t o = out_off(m, n);
+      finish(v, *reinterpret_cast<const floatx4*>(bias + n), has_res ? load4(rres, o) : floatx4{0.f, 0.f, 0.f, 0.f}, o);
     }
   }
 }
@@ -312,26 +327,30 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) k_conv_f32(ConvArgs a) {
 }  // namespace
 
 bool conv_f32_ok(const ConvArgs& a) {
-  return !a.x2 && a.split == 1 && a.Cin % 4 == 0 && a.Cout % 8 == 0 && a.Kp % F32_BK == 0 &&
-         (int64_t)a.kh * a.kw * a.Cin / 4 + 64 < (1 << 22);
+  return !a.x2 && a.split == 1 && a.Cin % 4 == 0 && a.Cout % 8 == 0 && a.Kp % F32_BK == 0;
 }
 
 void launch_conv_f32(const ConvArgs& a, int bm, int bn, int ks, hipStream_t s) {
   const int tiles = ((a.M + bm - 1) / bm) * ((a.Cout + bn - 1) / bn) * a.Z;
   const bool uni = a.Cin % F32_BK == 0 &&
                    ((int64_t)a.B * a.H * a.W + a.pad * (a.W + 1)) * a.Cin * 4 < (1ll << 31);
-#define FS_F32(FMv, FNv, WMv, WNv, KSv, Sv)                                                                        \
-  if (bm == 32 * FMv * WMv && bn == 32 * FNv * WNv && ks == KSv) {                                                 \
-    if (uni)                                                                                                       \
-      hipLaunchKernelGGL((k_conv_f32<FMv, FNv, WMv, WNv, KSv, Sv, true>), dim3(tiles), dim3(64 * WMv * WNv * KSv), \
-                         0, s, a);                                                                                 \
-    else                                                                                                           \
-      hipLaunchKernelGGL((k_conv_f32<FMv, FNv, WMv, WNv, KSv, Sv, false>), dim3(tiles), dim3(64 * WMv * WNv * KSv), \
-                         0, s, a);                                                                                 \
-    return;                                                                                                        \
+  const bool wide = (int64_t)a.kh * a.kw * a.Cin / 4 + 64 >= (1 << 22) || (int64_t)a.kh * a.W + a.kw >= (1 << 23);
+#define FS_FORM(FMv, FNv, WMv, WNv, KSv, Sv, FORMv)                                                            \
+  hipLaunchKernelGGL((k_conv_f32<FMv, FNv, WMv, WNv, KSv, Sv, FORMv>), dim3(tiles), dim3(64 * WMv * WNv * KSv), \
+                     0, s, a)
+#define FS_F32(FMv, FNv, WMv, WNv, KSv, Sv)                                         \
+  if (bm == 32 * FMv * WMv && bn == 32 * FNv * WNv && ks == KSv) {                  \
+    if (uni)                                                                        \
+      FS_FORM(FMv, FNv, WMv, WNv, KSv, Sv, F32_UNI);                                \
+    else if (wide)                                                                  \
+      FS_FORM(FMv, FNv, WMv, WNv, KSv, Sv, F32_WIDE);                               \
+    else                                                                            \
+      FS_FORM(FMv, FNv, WMv, WNv, KSv, Sv, F32_GEN);                                \
+    return;                                                                         \
   }
   FS_F32(1, 1, 2, 2, 1, 3) FS_F32(1, 1, 1, 1, 4, 2) FS_F32(1, 1, 1, 1, 8, 2) FS_F32(1, 1, 2, 1, 1, 2) FS_F32(1, 1, 4, 1, 1, 2)
 #undef FS_F32
+#undef FS_FORM
 }
 
 // The tile of a layer: 64x64 (0), 32x32 with the reduction over four (1) or

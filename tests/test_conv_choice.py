@@ -27,3 +27,8 @@ def test_fp32_layers_do_not_run_on_half_empty_tiles(cin, cout, k, hw, B, Z):
 ])
 def test_fp32_layers_whose_channels_fill_the_tile(cin, cout, hw, B, Z, want):
     assert fsb.fs_test_conv_choice(B, hw, hw, cin, cout, 3, 1, 1, fsb.FS_F32, Z) == (want, 1)
+
+
+def test_fp32_filters_of_any_size_have_a_kernel():
+    # a reduction of 2^24 values was refused while the kernel's index arithmetic had no form for it
+    assert fsb.fs_test_conv_choice(1, 2048, 2048, 4, 8, 2048, 1, 0, fsb.FS_F32)[1] == 1

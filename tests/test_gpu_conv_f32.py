@@ -37,3 +37,17 @@ def test_every_tile_matches_the_oracle(gpu_lib, ci):
         # fp32 sums in another order than the oracle's double sums, as for every fp32 conv
         assert np.all(np.abs(g - o) <= 1e-5 * ab + 1e-6), (ci, t, np.abs(g - o).max())
         assert np.array_equal(g, fsb.fs_test_conv(x, w, b, r, s, p, relu, F32, tile=t)), (ci, t)
+
+
+@pytest.mark.parametrize("H,W,k,stride", [
+    (3, 1 << 22, 3, 1 << 16),   # a filter that spans 3 x 2^22 pixels: row * width needs more than 24 bits
+    (2048, 2048, 2048, 1),      # a reduction of 2^24 stored values
+])
+def test_filters_beyond_24_bit_arithmetic(gpu_lib, H, W, k, stride):
+    rng = np.random.default_rng(k)
+    x = rng.standard_normal((1, H, W, 3), np.float32)
+    w = rng.standard_normal((8, k, k, 3), np.float32)
+    b = rng.standard_normal(8).astype(np.float32)
+    o, ab = oracle.conv2d(x, w, b, stride, 0, 0, None, "fp32", want_abs=True)
+    g = fsb.fs_test_conv(x, w, b, None, stride, 0, 0, F32)
+    assert np.all(np.abs(g - o) <= 1e-5 * ab + 1e-6), np.abs(g - o).max()
