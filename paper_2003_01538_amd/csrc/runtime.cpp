@@ -980,6 +980,13 @@ int batch_bucket(int B, int max_batch) {
   return std::min(b, max_batch);
 }
 
+// The smallest batch that uses a bucket's tiles.
+int bucket_min(int bucket) {
+  int b = 1;
+  while (b < bucket) b <<= 1;
+  return b / 2 + 1;
+}
+
 // Conv tiles for one batch bucket.  With tuning on, every candidate tile
 // of a layer is timed (HIP events, two launches after a warm-up) on the
 // layer's own buffers and the fastest kept.  Candidates are restricted to one
@@ -1030,6 +1037,14 @@ const std::vector<std::vector<int>>& tiles_for(fs_ensemble* e, int B, hipStream_
     for (size_t li = 0; li < g.layers.size(); ++li) {
       LayerPlan& P = g.layers[li];
       if (P.op != FS_OP_CONV || P.pool_fused || P.proj_into >= 0) continue;
+      // two layers that run in one launch at every batch of the bucket (from some
+      // batch on they always do) need no tile of their own
+      const int least = bucket_min(bucket);
+      ConvArgs d;
+      if (pair_args(e, g, P, (int)li, least, conv_args(e, g, P, least, nullptr, 0), &d)) {
+        ++li;
+        continue;
+      }
       ConvArgs a = conv_args(e, g, P, bucket, slot_ptr(g, P.out_slot), (int64_t)g.slot_elems[P.out_slot] * e->max_batch);
       const size_t need = conv_partial_floats(a) * 4;
       if (need > (g.conv_partial.p ? g.conv_partial.bytes : e->conv_partial.bytes))

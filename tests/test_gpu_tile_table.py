@@ -68,3 +68,26 @@ def test_retiming_times_the_table_tile_first(monkeypatch):
                 checked += 1
     assert checked >= 10
 
+
+
+def test_layers_that_run_in_one_launch_are_not_timed(monkeypatch):
+    # one ResNet-50: from nine images on its 56 x 56 blocks' widening and narrowing
+    # 1x1 convs always share a launch, so no batch of the 16-image bucket uses a
+    # tile of theirs; in the 8-image bucket five images still do
+    monkeypatch.setenv("FS_TUNE", "1")
+    w = wl.workload("resnet50x5_bf16_b256")
+    with fsb.Ensemble(w["models"][:1], w["out_hw"], wl.IMAGENET_MEAN, wl.IMAGENET_STD, w["precision"],
+                      max_batch=16) as ens:
+        timed = {}
+        for b in (8, 16):
+            imgs = list(wl.images_uniform(w["image_seed"], b, *w["in_hw"]))
+            fsb.fs_profile_enable(ens.handle)
+            ens.infer(imgs, want_logits=False)
+            pairs = {l["layer"] for l in fsb.fs_profile_launches(ens.handle) if l["kernel"] == "conv_pair_1x1"}
+            fsb.fs_profile_enable(ens.handle, False)
+            log = fsb.fs_tuning_log(ens.handle)
+            timed[b] = {int(m.group(1)) for m in re.finditer(rf"choice bucket {b} group 0 layer (\d+)", log)}
+            assert pairs, b
+            both = pairs | {i + 1 for i in pairs}
+            assert both <= timed[b] if b == 8 else not both & timed[b], (b, both, timed[b])
+        assert timed[8] - timed[16] == both
