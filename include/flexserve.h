@@ -315,7 +315,8 @@ fs_status fs_test_preprocess(const fs_image *imgs, int32_t B, int32_t out_h, int
 /* Convolution with fused epilogue: out = relu?(conv(in, w) + bias + res).
  * in [B][H][W][Cin], w [Cout][kh][kw][Cin], bias [Cout] or NULL,
  * res [B][Ho][Wo][Cout] or NULL, out [B][Ho][Wo][Cout].  tile = -1 picks
- * the tile the planner would, otherwise forces tile configuration `tile`. */
+ * the tile that fs_conv_bf16_device_noalloc would (fp32: the planner's),
+ * otherwise forces tile configuration `tile`. */
 fs_status fs_test_conv(const float *in, int32_t B, int32_t H, int32_t W, int32_t Cin,
                        const float *w, const float *bias, const float *res, int32_t Cout,
                        int32_t kh, int32_t kw, int32_t stride, int32_t pad, int32_t relu,
@@ -328,8 +329,9 @@ fs_status fs_test_conv(const float *in, int32_t B, int32_t H, int32_t W, int32_t
  * fs_conv_bf16_device_noalloc (bf16, Z = 1), whose caller has the packed rows
  * only.  FS_ERR_UNSUPPORTED where no kernel takes the layer.  Needs no GPU. */
 fs_status fs_test_conv_choice(int32_t B, int32_t H, int32_t W, int32_t Cin, int32_t Cout, int32_t kh,
-                              int32_t kw, int32_t stride, int32_t pad, int32_t precision, int32_t Z,
-                              int32_t packed, int32_t num_cus, int32_t *tile, int32_t *split);
+                              int32_t kw, int32_t stride, int32_t pad, int32_t residual,
+                              int32_t precision, int32_t Z, int32_t packed, int32_t num_cus,
+                              int32_t *tile, int32_t *split);
 
 /* A widening 1x1 conv and the narrowing 1x1 conv that reads it, bf16, both
  * with ReLU: y = relu(w1 . [in | in2 at stride2] + bias1 + res), out =

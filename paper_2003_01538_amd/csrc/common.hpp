@@ -93,6 +93,7 @@ bool conv_tile_ok(Prec p, int t, const ConvArgs& a);         // the tile's kerne
 bool conv_tile_candidate(Prec p, int t, const ConvArgs& a);  // ... and is among its automatic choices
 bool conv_dma_ok(const ConvArgs& a);
 void launch_conv_dma(const ConvArgs& a, int bm, int bn, int waves, int wgm, int stages, hipStream_t s);
+int conv_dma_pick(const ConvArgs& a, int num_cus, double* us);  // LDS-DMA tile and its estimated time (without the completion of a split)
 bool conv_f32_ok(const ConvArgs& a);   // fp32: every planned layer
 int conv_f32_tile(const ConvArgs& a);  // ... and the tile that runs it
 void launch_conv_f32(const ConvArgs& a, int bm, int bn, int ks, hipStream_t s);

@@ -348,33 +348,34 @@ int conv_ks_tile(Prec p, const ConvArgs& a) {
 }
 
 // Time in us of a layer on an LDS-DMA tile, for the tiles worth choosing
-// without timing them: a + b nk + (c nk + d) ceil(n) + (e nk + f) n, with nk
-// K-tiles per workgroup and n workgroups per CU (at least one), each
-// coefficient fitted (non-negative, least squares of the relative error, 4 to
-// 13 % rms) to 234 measured launches: 3x3 and 1x1 layers of 64 to 2048
-// channels, stride 1 and 2, maps of 7 to 112, B = 1 to 32, with and without
-// the weights in fragment order.  The tile it picks is on average 2.5 % slower
-// than the fastest of all twenty; a rule by the tiles' fill and reuse was 16 %
+// without timing them: a + b nk + c nk ceil(n / 2) + d ceil(n) + e nk n + f n + g n
+// (with a residual) + h nk min(1, n), with nk K-tiles per workgroup and n
+// workgroups per CU (at least one but in the last term), each coefficient
+// fitted (non-negative, least squares of the relative error, 6 to 9 % rms) to
+// 1286 measured launches: 3x3 and 1x1 layers of 64 to 2048 channels, stride 1 and
+// 2, maps of 3 to 117, B = 1 to 48, one to five models, with and without the
+// weights in fragment order.  The tile it picks is on average 1.7 % slower than
+// the fastest of all twenty; a rule by the tiles' fill and reuse was 30 %
 // (1x1, 64 -> 256 with a residual on 56x56, B = 32: 26 us on 64x128 instead of
 // 32 on 256x256; 3x3, 64 -> 128 on 112x112: 65 instead of 92).
 struct DmaCost {
   const char* tile;
   bool frag;  // with (true) or without fragment-ordered weights; the other tiles: the same either way
-  float a, b, c, d, e, f;
+  float a, b, c, d, e, f, g, h;
 };
 static const DmaCost kDmaCost[] = {
-    {"bf16dma3_64x64_w4_v8", true, 2.54f, 0.22f, 0.14f, 0.56f, 0.f, 0.52f},
-    {"bf16dma2_64x128_w4_v8", true, 2.61f, 0.19f, 0.19f, 0.78f, 0.f, 0.82f},
-    {"bf16dma1_64x128_w4_v8", true, 2.84f, 0.46f, 0.01f, 1.13f, 0.15f, 0.19f},
-    {"bf16dma2_128x64_w4_v8", true, 2.68f, 0.23f, 0.17f, 1.00f, 0.f, 0.82f},
-    {"bf16dma1_128x64_w4_v8", true, 2.92f, 0.46f, 0.04f, 1.12f, 0.09f, 0.52f},
-    {"bf16dma2_96x128_w4m1_v8", true, 3.14f, 0.36f, 0.03f, 0.97f, 0.15f, 1.07f},
-    {"bf16dma2_96x128_w4m1_v8", false, 2.19f, 0.30f, 0.08f, 1.17f, 0.18f, 1.57f},
-    {"bf16dma2_128x128_w4_v8", true, 2.24f, 0.37f, 0.14f, 1.00f, 0.13f, 2.51f},
-    {"bf16dma1_128x128_w4_v8", true, 3.27f, 0.64f, 0.f, 1.13f, 0.21f, 1.66f},
+    {"bf16dma3_64x64_w4_v8", true, 2.47f, 0.18f, 0.02f, 0.82f, 0.15f, 0.09f, 0.09f, 0.05f},
+    {"bf16dma2_64x128_w4_v8", true, 2.76f, 0.16f, 0.00f, 0.92f, 0.24f, 0.36f, 0.41f, 0.11f},
+    {"bf16dma1_64x128_w4_v8", true, 2.99f, 0.31f, 0.02f, 0.76f, 0.20f, 0.32f, 0.40f, 0.12f},
+    {"bf16dma2_128x64_w4_v8", true, 2.73f, 0.14f, 0.00f, 1.24f, 0.23f, 0.17f, 0.36f, 0.14f},
+    {"bf16dma1_128x64_w4_v8", true, 2.83f, 0.29f, 0.02f, 1.01f, 0.20f, 0.39f, 0.28f, 0.14f},
+    {"bf16dma2_96x128_w4m1_v8", true, 2.97f, 0.07f, 0.22f, 1.29f, 0.15f, 0.36f, 0.91f, 0.20f},
+    {"bf16dma2_96x128_w4m1_v8", false, 2.08f, 0.00f, 0.34f, 1.71f, 0.12f, 0.64f, 0.78f, 0.22f},
+    {"bf16dma2_128x128_w4_v8", true, 1.83f, 0.00f, 0.41f, 1.73f, 0.13f, 1.34f, 1.31f, 0.28f},
+    {"bf16dma1_128x128_w4_v8", true, 2.87f, 0.28f, 0.18f, 1.22f, 0.21f, 1.35f, 0.85f, 0.30f},
 };
 
-static int dma_pick(const ConvArgs& a, int num_cus) {
+int conv_dma_pick(const ConvArgs& a, int num_cus, double* us_out) {
   constexpr int N = sizeof(kDmaCost) / sizeof(DmaCost);
   static const std::array<int, N> index = [] {
     std::array<int, N> ix{};
@@ -390,14 +391,17 @@ static int dma_pick(const ConvArgs& a, int num_cus) {
     const ConvTile& c = conv_tile(BF16, t);
     if (c.wgm == 1 && k.frag != (a.wf != nullptr)) continue;
     const float nk = (float)(a.Kp / 64) / a.split;
-    const float n = std::max(1.f, (float)((a.M + c.bm - 1) / c.bm) * ((a.Cout + c.bn - 1) / c.bn) * a.Z * a.split / num_cus);
-    const float us = k.a + k.b * nk + (k.c * nk + k.d) * std::ceil(n) + (k.e * nk + k.f) * n;
+    const float fill = (float)((a.M + c.bm - 1) / c.bm) * ((a.Cout + c.bn - 1) / c.bn) * a.Z * a.split / num_cus;
+    const float n = std::max(1.f, fill);
+    const float us = k.a + k.b * nk + k.c * nk * std::ceil(0.5f * n) + k.d * std::ceil(n) + (k.e * nk + k.f) * n +
+                     (a.res ? k.g * n : 0.f) + k.h * nk * std::min(1.f, fill);
     if (best < 0 || us < best_t) { best = t; best_t = us; }
   }
+  if (us_out) *us_out = best_t;
   return best;
 }
 
-// The LDS-DMA tiles by dma_pick.  Within the other families the largest
+// The LDS-DMA tiles by conv_dma_pick.  Within the other families the largest
 // useful tile: prefer tiles that keep >= 2 workgroups per CU busy, then the
 // least padding waste, then the larger tile (more reuse per byte).
 int conv_pick_tile(Prec p, const ConvArgs& a, int num_cus, bool ks) {
@@ -409,7 +413,7 @@ int conv_pick_tile(Prec p, const ConvArgs& a, int num_cus, bool ks) {
   for (int t = 0; t < conv_num_tiles(p); ++t)
     if (conv_tile(p, t).halo != 4 && conv_tile_family(conv_tile(p, t)) > fam && !conv_tile_direct(conv_tile(p, t)) &&
         conv_tile_candidate(p, t, a)) fam = std::max(fam, conv_tile_family(conv_tile(p, t)));
-  if (fam == 1) return dma_pick(a, num_cus);
+  if (fam == 1) return conv_dma_pick(a, num_cus, nullptr);
   int best = -1;
   double best_score = -1;
   for (int t = 0; t < conv_num_tiles(p); ++t) {

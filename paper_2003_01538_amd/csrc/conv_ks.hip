@@ -369,6 +369,8 @@ KsGeom ks_geom(const ConvArgs& a, int bm, int bn, bool packed, size_t* lds) {
   return g;
 }
 
+constexpr size_t KS_LDS = 160 * 1024;
+
 }  // namespace
 
 // Layers the kernel can run: 3x3 (pad 1) or 1x1 (pad 0) filters of stride 1
@@ -389,8 +391,8 @@ bool conv_ks_ok(const ConvArgs& a, int bm, int bn) {
   if ((int64_t)a.B * a.H * a.W * a.Cin * 2 >= (1ll << 31) || (int64_t)a.Cout * a.Kp * 2 >= (1ll << 31)) return false;
   if (a.K / BK < KS_WAVES / (bn / 32)) return false;  // every wave has a K-tile
   size_t lds = 0;
-  ks_geom(a, bm, bn, false, &lds);  // the choice of kernel does not depend on the form of the weights
-  return lds <= 160 * 1024;
+  ks_geom(a, bm, bn, false, &lds);  // packed rows that find no LDS to be turned in are read as they lie
+  return lds <= KS_LDS;
 }
 
 void launch_conv_ks(const ConvArgs& a_in, int bm, int bn, hipStream_t s) {
@@ -399,7 +401,7 @@ void launch_conv_ks(const ConvArgs& a_in, int bm, int bn, hipStream_t s) {
   a.partial = nullptr;
   size_t lds = 0;
   KsGeom g = ks_geom(a, bm, bn, !a.wf, &lds);
-  const bool rows = lds > 160 * 1024;  // no room to turn packed rows
+  const bool rows = lds > KS_LDS;  // no room to turn packed rows
   if (rows) g = ks_geom(a, bm, bn, false, &lds);
   const dim3 grid((unsigned)(g.mt * g.nt * a.Z)), block(64 * KS_WAVES);
   // the turned weights take registers: a shorter ring
@@ -418,69 +420,122 @@ void launch_conv_ks(const ConvArgs& a_in, int bm, int bn, hipStream_t s) {
 }
 
 // The tiles of the rule below: pixels, channels, waves along the reduction,
-// the measured time of one K-tile of a wave (us), and whether its registers
-// let two workgroups share a CU.
+// whether registers let two workgroups share a CU, the most workgroups per CU at
+// which the tile was the fastest kernel anywhere, and the time in us with
+// fragment-ordered weights and with packed rows turned through LDS,
+//   a + (b q + c + l lds / 80 KB + r residual) f,
+// q: K-tiles per wave, f: 1 for up to one workgroup a CU; beyond that, for n of
+// them, one * ceil(n) where LDS holds one at a time, else max(two, slope n).
+// rows: packed rows read as they lie take that many times as long as fragments.
+struct KsCost {
+  double a, b, c, l, one, two, slope, r;
+};
 struct KsTile {
-  int bm, bn, ks;
-  double us;
-  int two;
+  int bm, bn, ks, pair;
+  double most;
+  KsCost frag, turn;
+  double rows;
 };
 static const KsTile kKsTiles[] = {
-    {32, 32, 8, 0.27, 1}, {32, 64, 4, 0.25, 1}, {64, 64, 4, 0.37, 1}, {64, 128, 2, 0.36, 1}, {96, 128, 2, 0.62, 0}};
+    {32, 32, 8, 1, 3, {2.96, 0.22, 0.77, 2.06, 1.20, 1.79, 1.11, 0.18}, {3.11, 0.42, 0.00, 2.56, 1.11, 2.17, 1.42, 0.00}, 1.70},
+    {32, 64, 4, 1, 2, {3.07, 0.23, 0.60, 2.12, 1.14, 1.88, 1.17, 0.04}, {3.19, 0.41, 0.00, 2.38, 1.10, 2.15, 1.31, 0.00}, 2.00},
+    {64, 64, 4, 1, 2, {3.01, 0.34, 0.25, 2.10, 1.21, 1.66, 1.10, 0.09}, {2.74, 0.57, 0.00, 2.54, 1.12, 1.60, 1.15, 0.00}, 1.45},
+    {64, 128, 2, 1, 2, {2.94, 0.35, 0.61, 2.05, 1.16, 1.77, 1.16, 0.10}, {3.05, 0.59, 0.00, 2.52, 1.06, 1.81, 1.22, 0.00}, 1.70},
+    {96, 128, 2, 0, 2, {1.38, 0.50, 2.48, 2.67, 1.05, 1.39, 1.15, 0.42}, {1.00, 0.71, 2.37, 3.05, 1.01, 2.24, 1.15, 0.31}, 1.40},
+};
 
-// Estimated time (us) of the layer on this kernel: a launch, then rounds of
-// workgroups, each its share of the K-tiles plus the staging of its input.
-static double ks_estimate(const ConvArgs& a, const KsTile& t, double cus) {
+// Estimated time (us) of the layer on a tile, with the weights in the form that
+// the layer has them in; *rounds: more than one workgroup a CU.
+static double ks_estimate(const ConvArgs& a, const KsTile& t, double cus, bool* rounds) {
   size_t lds = 0;
   const KsGeom g = ks_geom(a, t.bm, t.bn, false, &lds);
-  const double r = (double)g.mt * g.nt * a.Z / cus;
-  const int nk = a.K / BK, per_cu = std::min(t.two ? 2 : 1, (int)(160 * 1024 / lds));
-  const double wg = (nk + t.ks - 1) / t.ks * t.us + 0.9 + (double)lds / (80 * 1024);
-  if (r > 3) return 1e30;  // outside what was measured
-  return 3.6 + wg * (r <= 1 ? 1.0 : per_cu == 1 ? std::ceil(r) : std::max(1.5, 1.1 * r));
+  const double n = (double)g.mt * g.nt * a.Z / cus;
+  *rounds = n > 1;
+  if (n > t.most) return 1e30;
+  bool turn = false;
+  if (!a.wf) {
+    size_t with = 0;
+    ks_geom(a, t.bm, t.bn, true, &with);
+    turn = with <= KS_LDS;
+  }
+  const KsCost& c = turn ? t.turn : t.frag;
+  const int nk = a.K / BK, per_cu = std::min(t.pair ? 2 : 1, (int)(KS_LDS / lds));
+  const double wg = (nk + t.ks - 1) / t.ks * c.b + c.c + c.l * (double)lds / (80 * 1024) + (a.res ? c.r : 0.0);
+  const double us = c.a + wg * (n <= 1 ? 1.0 : per_cu == 1 ? c.one * std::ceil(n) : std::max(c.two, c.slope * n));
+  return a.wf || turn ? us : us * t.rows;
 }
 
-// The same for the kernel that would run the layer otherwise.
-static double other_estimate(const ConvArgs& a, double cus) {
-  const int nk = a.K / BK;
-  const double t96 = (double)((a.M + 95) / 96) * ((a.Cout + 127) / 128) * a.Z;  // 96 x 128 tiles
-  if (conv_hs_chosen(a)) return 4.0 + nk * 0.37 * std::max(1.0, t96 / cus);
+// The time below which this kernel is taken: that of the kernel that runs the
+// layer otherwise, less what the estimates may be off.  An ensemble's implicit
+// GEMM runs in the fastest of twenty timed tiles, of which nine are estimated.
+static double ks_limit(const ConvArgs& a, double cus) {
+  const double nk = a.K / BK;
+  if (conv_hs_chosen(a)) {
+    auto per_cu = [&](int bm) { return std::max(1.0, (double)((a.M + bm - 1) / bm) * (a.Cout / 128) * a.Z / cus); };
+    // the register-weight tiles' patch, nearly: their rows, a partial one at
+    // either end, the rows above and below, and the rows between two images
+    auto fits = [&](int bm) { return (bm / a.W + 4) * (a.W + 2) <= 320; };
+    const double n = per_cu(128), n96 = per_cu(96), n160 = per_cu(160);
+    const double hs = 1.91 + (0.387 * nk + 2.31) * std::ceil(n) + (1.87 + (a.res ? 0.10 : 0.0)) * n;
+    if (!a.wf) return 0.97 * hs;
+    const double e96 = 3.10 + 0.032 * nk + (0.144 * nk + 1.33) * std::ceil(n96) + (0.154 * nk + 1.50) * n96;
+    const double e160 = 2.26 + 0.137 * nk + 0.137 * nk * std::ceil(n160) + (0.311 * nk + 7.28) * n160;
+    double us = a.x2 ? e96 : hs;  // a projection shortcut runs in the register-weight form only
+    if (fits(96)) us = std::min(us, e96);
+    if (fits(160)) us = std::min(us, e160);
+    return 0.97 * us;
+  }
   if (conv_halo_ok(a, 4, 56, 64))
     return 4.6 + 4.1 * std::ceil((double)a.B * ((a.Ho + 3) / 4) * (a.Cout / 64) * a.Z / cus);
-  const int split = conv_split(BF16, a, (int)cus);
-  const double t = t96 * split, k = (double)nk / split;
-  double us = 4.5 + (t >= cus ? (k * 0.42 + 1.0) * t / cus : k * 0.25 + 1.0);
-  if (split > 1) us += 3.0 + (double)split * a.M * a.Cout * a.Z * 8 / 6.5e6;  // the completion: partial sums out and in
-  return us;
+  ConvArgs d = a;
+  d.split = conv_split(BF16, a, (int)cus);
+  double us = 0;
+  conv_dma_pick(d, (int)cus, &us);
+  if (d.split > 1) us += 3.0 + (double)d.split * a.M * a.Cout * a.Z * 8 / 6.5e6;  // the completion: partial sums out and in
+  return (a.wf ? 0.91 : 0.97) * us;
 }
 
-// Which of this kernel's tiles runs the layer, or -1.  The estimates above
-// were fitted to back-to-back launches of every tile on ten layer shapes of
-// ResNet-18 and ResNet-50 at 1 to 64 images and one or three models (100
-// cases).  The rule picks within 6 % of the fastest kernel in 94 of them and
-// within 21 % in all.  Measured (us, this kernel against the one that ran
-// before): 7x7x512 3x3, three models, B = 1 / 8 / 16: 7.3 / 12.4 / 17.6
-// against 26.3 / 32.4 / 32.5; 14x14x256 B = 1 / 8: 6.1 / 11.3 against 15.9 /
-// 16.6; 28x28x128 to 256 stride 2 (split over workgroups before), B = 8 / 16:
-// 9.3 / 12.7 against 16.9 / 22.5.  With more tiles the other kernels win:
-// 14x14x256 B = 32 24.6 against 26.4, 28x28x128 to 256 stride 2 17.3 against
-// 24.0.  It depends on the shape and the batch only (256 CUs, the chip's),
-// never on timing, so a result's bits do not vary from run to run.
+// Which of this kernel's tiles runs the layer, or -1: the one that is estimated
+// fastest, if that beats the kernel that runs the layer otherwise, with the
+// weights in the form the layer has them in.  The estimates were fitted to
+// back-to-back launches of every tile and of every other kernel in both forms
+// on 820 layers: 64 to 2048 channels, 3x3 and 1x1, stride 1 and 2, maps of 3 to
+// 117, B = 1 to 48, one to five models.  The rule is 0.3 % slower there than the
+// fastest kernel on average, and nowhere more than 3 % slower than the kernel
+// that ran the layer otherwise at its fastest tile (packed rows: against that
+// kernel at the tile it gets).  Measured (us, this kernel against the other):
+// 7x7x512 3x3, three models, B = 1 / 8 / 16: 7.3 / 12.4 / 17.6 against 26.3 / 32.4 /
+// 32.5; 14x14x256 B = 1 / 8: 6.1 / 11.3 against 15.9 / 16.6; 28x28x128 to 256
+// stride 2 (split over workgroups), B = 8 / 16: 9.3 / 12.7 against 16.9 / 22.5.
+// The others win with more tiles (14x14x256 B = 32 24.6 against 26.4; 28x28x128
+// to 256 stride 2 17.3 against 24.0), where rounds of workgroups fill a CU's LDS
+// one at a time (14x14x512, B = 12, five models, 51 against 64), where the
+// reduction is two K-tiles (1x1, 128 -> 512 on 28x28, 4.4 against 5.3), and with
+// packed rows that find no LDS to be turned in (28x28x512, B = 10, 40 against 73).
+// It depends on the shape and the batch only (256 CUs, the chip's), never on
+// timing, so a result's bits do not vary from run to run.
 int conv_ks_pick(const ConvArgs& a_in, int* bm, int* bn) {
   constexpr double cus = 256;
   ConvArgs a = a_in;
   a.split = 1;  // the caller's split is the implicit GEMM's
-  double best = 1e30;
+  double best = 1e30, us = 1e30;
   int pick = -1;
   for (int i = 0; i < (int)(sizeof(kKsTiles) / sizeof(KsTile)); ++i) {
     if (!conv_ks_ok(a, kKsTiles[i].bm, kKsTiles[i].bn)) continue;
-    const double e = ks_estimate(a, kKsTiles[i], cus);
-    if (e < best) {
-      best = e;
+    bool rounds = false;
+    const double e = ks_estimate(a, kKsTiles[i], cus, &rounds);
+    // in a network, whose weights are not in L2 again when a launch starts, more
+    // workgroups cost more than in a loop: of nearly equal tiles the larger one
+    // (14x14x256, B = 32: 64x64 12.5 us in a loop and 15.4 among the other
+    // layers, 64x128 12.4 and 14.4)
+    const double key = rounds && a.wf ? 1.05 * e : e;
+    if (key < best) {
+      best = key;
+      us = e;
       pick = i;
     }
   }
-  if (pick < 0 || best >= 0.97 * other_estimate(a, cus)) return -1;
+  if (pick < 0 || us >= ks_limit(a, cus)) return -1;
   *bm = kKsTiles[pick].bm;
   *bn = kKsTiles[pick].bn;
   return pick;

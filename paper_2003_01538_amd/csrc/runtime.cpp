@@ -286,6 +286,8 @@ struct fs_ensemble {
   bool pass_pending = false;
   // conv tile per (batch bucket) -> per group -> per layer, measured once
   std::map<int, std::vector<std::vector<int>>> tiles;
+  // the same per batch size, with the layers whose tile follows the batch (at most max_batch entries)
+  std::map<int, std::vector<std::vector<int>>> batch_tiles;
   // tile choice: 0 = committed table, else the shape rule (no timing);
   // 1 = time every candidate; 2 (default) = the table, timing what it lacks
   int tune = 2;
@@ -1021,8 +1023,7 @@ int table_tile(const fs_ensemble* e, const ConvArgs& a, int bucket, int fam) {
   return -1;
 }
 
-const std::vector<std::vector<int>>& tiles_for(fs_ensemble* e, int B, hipStream_t s) {
-  const int bucket = batch_bucket(B, e->max_batch);
+const std::vector<std::vector<int>>& bucket_tiles(fs_ensemble* e, int bucket, hipStream_t s) {
   auto it = e->tiles.find(bucket);
   if (it != e->tiles.end()) return it->second;
   std::vector<std::vector<int>> choice(e->groups.size());
@@ -1055,17 +1056,27 @@ const std::vector<std::vector<int>>& tiles_for(fs_ensemble* e, int B, hipStream_
         e->workspace_bytes += (int64_t)e->conv_partial.bytes;
         a.partial = static_cast<float*>(e->conv_partial.p);
       }
-      // an fp32 layer, and a bf16 layer of few tiles (its reduction split over
-      // a workgroup's waves), run in the one tile their rules name: nothing to
-      // time (FS_TUNE=1, which times every layer, times that tile)
-      const int ruled = conv_pick_tile(e->prec, a, e->num_cus);
-      if (e->tune != 1 && ruled >= 0 && (e->prec == F32 || conv_tile_family(conv_tile(e->prec, ruled)) == 4)) {
+      // an fp32 layer, and a bf16 layer of few tiles at every batch of the bucket
+      // (its reduction split over a workgroup's waves), run in the tiles their
+      // rules name: nothing to time (FS_TUNE=1, which times every layer, times
+      // that tile).  A layer of few tiles at some batches only gets a tile for
+      // the others here.
+      bool always = e->prec == F32;
+      if (!always) {
+        always = true;
+        for (int b = least; b <= bucket && always; ++b) always = conv_ks_tile(BF16, conv_args(e, g, P, b, nullptr, 0)) >= 0;
+      }
+      const int ruled = conv_pick_tile(e->prec, a, e->num_cus, always);
+      if (e->tune != 1 && ruled >= 0 && always) {
         choice[gi][li] = ruled;
         continue;
       }
+      auto candidate = [&](int t) {
+        return conv_tile_candidate(e->prec, t, a) && (always || conv_tile_family(conv_tile(e->prec, t)) != 4);
+      };
       int fam = -1;  // the layer runs in the highest kernel family among its candidates
       for (int t = 0; t < conv_num_tiles(e->prec); ++t)
-        if (conv_tile_candidate(e->prec, t, a)) fam = std::max(fam, conv_tile_family(conv_tile(e->prec, t)));
+        if (candidate(t)) fam = std::max(fam, conv_tile_family(conv_tile(e->prec, t)));
       int best = ruled;
       const int from_table = e->tune == 1 ? -1 : table_tile(e, a, bucket, fam);
       if (from_table >= 0) best = from_table;
@@ -1075,8 +1086,7 @@ const std::vector<std::vector<int>>& tiles_for(fs_ensemble* e, int B, hipStream_
         std::vector<int> order;
         if (e->tune == 3 && from_table >= 0) order.push_back(from_table);
         for (int t = 0; t < conv_num_tiles(e->prec); ++t)
-          if (conv_tile_candidate(e->prec, t, a) && conv_tile_family(conv_tile(e->prec, t)) == fam &&
-              !(e->tune == 3 && t == from_table))
+          if (candidate(t) && conv_tile_family(conv_tile(e->prec, t)) == fam && !(e->tune == 3 && t == from_table))
             order.push_back(t);
         float best_ms = 1e30f;
         for (int t : order) {
@@ -1112,6 +1122,26 @@ const std::vector<std::vector<int>>& tiles_for(fs_ensemble* e, int B, hipStream_
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   return e->tiles.emplace(bucket, std::move(choice)).first->second;
+}
+
+// The tiles of a pass of B images: its bucket's, except for layers whose tile a
+// rule names (fp32, and a reduction split over a workgroup's waves), which get
+// the one for B itself.  A layer's workgroups come in whole rounds of 256, so the
+// bucket's tile can be a bad one for fewer images: three ResNet-18s, twelve
+// images, 14x14x256 on the tile for sixteen 19.5 us instead of 15.8.
+const std::vector<std::vector<int>>& tiles_for(fs_ensemble* e, int B, hipStream_t s) {
+  auto it = e->batch_tiles.find(B);
+  if (it != e->batch_tiles.end()) return it->second;
+  auto choice = bucket_tiles(e, batch_bucket(B, e->max_batch), s);
+  for (size_t gi = 0; gi < choice.size(); ++gi)
+    for (size_t li = 0; li < choice[gi].size(); ++li) {
+      if (choice[gi][li] < 0) continue;
+      Group& g = e->groups[gi];
+      const ConvArgs a = conv_args(e, g, g.layers[li], B, nullptr, 0);
+      const int ruled = e->prec == F32 ? conv_pick_tile(F32, a, e->num_cus) : conv_ks_tile(BF16, a);
+      if (ruled >= 0) choice[gi][li] = ruled;
+    }
+  return e->batch_tiles.emplace(B, std::move(choice)).first->second;
 }
 
 // Test-only: copy image e->dbg_image of layer li's stored output, for every
@@ -1318,8 +1348,8 @@ int launches_per_pass(fs_ensemble* e) {
   int n = 1 + (e->need_plain ? 1 : 0) + (e->need_s2d ? 1 : 0);  // preprocess + softmax/combine
   for (Group& g : e->groups) {
     const std::vector<std::vector<int>>* tl = nullptr;
-    auto it = e->tiles.find(batch_bucket(e->max_batch, e->max_batch));
-    if (it != e->tiles.end()) tl = &it->second;
+    auto it = e->batch_tiles.find(e->max_batch);
+    if (it != e->batch_tiles.end()) tl = &it->second;
     bool skip_next = false;
     for (size_t li = 0; li < g.layers.size(); ++li) {
       LayerPlan& P = g.layers[li];
@@ -2192,7 +2222,11 @@ static void run_test_conv(const float* in, int32_t B, int32_t H, int32_t W, int3
       return;
     }
     int tl = tile;
-    if (tl < 0) tl = conv_pick_tile(p, a, num_cus_of(device));
+    if (tl < 0) {  // as the allocation-free entry point, whose caller has packed weights only
+      ConvArgs q = a;
+      q.wf = nullptr;
+      tl = conv_pick_tile(p, q, num_cus_of(device));
+    }
     if (!conv_tile_ok(p, tl, a)) fail(FS_ERR_UNSUPPORTED, "tile " + std::to_string(tile) + " does not fit this conv");
     if (conv_tile_direct(conv_tile(p, tl))) {  // the ensemble's split rule, so split-K is exercised too
       a.split = conv_split(p, a, num_cus_of(device));
@@ -2215,8 +2249,8 @@ fs_status fs_test_conv(const float* in, int32_t B, int32_t H, int32_t W, int32_t
 }
 
 fs_status fs_test_conv_choice(int32_t B, int32_t H, int32_t W, int32_t Cin, int32_t Cout, int32_t kh, int32_t kw,
-                              int32_t stride, int32_t pad, int32_t precision, int32_t Z, int32_t packed,
-                              int32_t num_cus, int32_t* tile, int32_t* split) {
+                              int32_t stride, int32_t pad, int32_t residual, int32_t precision, int32_t Z,
+                              int32_t packed, int32_t num_cus, int32_t* tile, int32_t* split) {
   return guarded(nullptr, [&] {
     const Prec p = prec_of(precision);
     if (!tile || !split || B < 1 || H < 1 || W < 1 || Cin < 1 || Cout < 1 || kh < 1 || kw < 1 || stride < 1 || pad < 0 ||
@@ -2228,7 +2262,8 @@ fs_status fs_test_conv_choice(int32_t B, int32_t H, int32_t W, int32_t Cin, int3
     a.Ho = (H + 2 * pad - kh) / stride + 1; a.Wo = (W + 2 * pad - kw) / stride + 1;
     a.kh = kh; a.kw = kw; a.stride = stride; a.pad = pad;
     a.K = kh * kw * a.Cin; a.Kp = (int)round_up(a.K, CONV_KPAD); a.M = B * a.Ho * a.Wo; a.Z = Z;
-    if (!packed && conv_frag_wanted(p, Cout, a.Kp)) a.wf = &a;  // only asked whether it is there
+    if (!packed && conv_frag_wanted(p, Cout, a.Kp)) a.wf = &a;  // only asked whether they are there
+    if (residual) a.res = &a;
     a.split = conv_split(p, a, num_cus);
     *tile = conv_pick_tile(p, a, num_cus);
     if (*tile < 0 || !conv_tile_ok(p, *tile, a)) fail(FS_ERR_UNSUPPORTED, "no conv kernel takes this shape");

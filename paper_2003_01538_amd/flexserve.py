@@ -121,7 +121,7 @@ SIGNATURES = [
                                     _fp, _fp, _fp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                                     ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                                     ctypes.c_int32, _fp, ctypes.c_int32]),
-    ("fs_test_conv_choice", ctypes.c_int, [ctypes.c_int32] * 13 + [_i32p] * 2),
+    ("fs_test_conv_choice", ctypes.c_int, [ctypes.c_int32] * 14 + [_i32p] * 2),
     ("fs_test_conv_pair", ctypes.c_int, [_fp] + [ctypes.c_int32] * 4 + [_fp] + [ctypes.c_int32] * 4 +
                                         [_fp, _fp, _fp, ctypes.c_int32, _fp, _fp, ctypes.c_int32, ctypes.c_int32,
                                          _fp, _fp, ctypes.c_int32]),
@@ -425,11 +425,12 @@ def fs_test_conv(x, w, bias, res, stride, pad, relu, precision, tile=-1, device=
     return out
 
 
-def fs_test_conv_choice(B, H, W, Cin, Cout, k, stride, pad, precision, Z=1, packed=False, num_cus=256):
+def fs_test_conv_choice(B, H, W, Cin, Cout, k, stride, pad, precision, Z=1, packed=False, residual=False,
+                        num_cus=256):
     """(name of the tile, split) of a layer where nothing is timed; needs no GPU."""
     tile, split = ctypes.c_int32(), ctypes.c_int32()
-    _check(load().fs_test_conv_choice(B, H, W, Cin, Cout, k, k, stride, pad, precision, Z, int(packed), num_cus,
-                                      ctypes.byref(tile), ctypes.byref(split)))
+    _check(load().fs_test_conv_choice(B, H, W, Cin, Cout, k, k, stride, pad, int(residual), precision, Z,
+                                      int(packed), num_cus, ctypes.byref(tile), ctypes.byref(split)))
     return fs_conv_tile_name(precision, tile.value), split.value
 
 

@@ -32,3 +32,25 @@ def test_fp32_layers_whose_channels_fill_the_tile(cin, cout, hw, B, Z, want):
 def test_fp32_filters_of_any_size_have_a_kernel():
     # a reduction of 2^24 values was refused while the kernel's index arithmetic had no form for it
     assert fsb.fs_test_conv_choice(1, 2048, 2048, 4, 8, 2048, 1, 0, fsb.FS_F32)[1] == 1
+
+
+# Layers whose reduction could be split over a workgroup's waves, and the kernel that was measured faster.
+@pytest.mark.parametrize("B,hw,cin,cout,k,stride,Z,packed,residual,split", [
+    (1, 7, 512, 512, 3, 1, 3, False, True, True),       # few tiles: 7.3 us against 26.3
+    (8, 28, 128, 256, 3, 2, 1, False, False, True),     # ... and a split over workgroups saved: 9.3 against 16.9
+    (8, 28, 128, 256, 3, 2, 1, True, False, True),
+    (1, 7, 512, 512, 3, 1, 1, True, True, True),
+    (1, 28, 128, 512, 1, 1, 2, False, True, False),     # two K-tiles: 5.3 us against 4.4
+    (4, 12, 128, 384, 1, 2, 1, False, False, False),
+    (12, 14, 512, 512, 3, 1, 5, False, False, False),   # three rounds of one workgroup a CU: 64 us against 51
+    (7, 28, 512, 512, 3, 1, 2, False, False, False),    # 63 us against 51
+    (6, 16, 2048, 512, 1, 1, 2, False, True, False),    # 29 us against 22
+    (12, 31, 512, 512, 3, 1, 1, True, False, False),    # packed rows that find no LDS to be turned in: 109 us against 67
+    (10, 28, 512, 512, 3, 1, 1, True, False, False),    # 73 us against 40
+    (4, 28, 512, 512, 3, 1, 1, True, False, False),     # 37 us against 34
+    (20, 17, 512, 512, 3, 1, 1, True, False, False),    # 39 us against 35
+])
+def test_the_split_reduction_kernel_takes_the_layers_it_is_faster_on(B, hw, cin, cout, k, stride, Z, packed, residual,
+                                                                     split):
+    name, _ = fsb.fs_test_conv_choice(B, hw, hw, cin, cout, k, stride, k // 2, fsb.FS_BF16, Z, packed, residual)
+    assert ("ks_" in name) == split, name

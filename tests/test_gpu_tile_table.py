@@ -91,3 +91,18 @@ def test_layers_that_run_in_one_launch_are_not_timed(monkeypatch):
             both = pairs | {i + 1 for i in pairs}
             assert both <= timed[b] if b == 8 else not both & timed[b], (b, both, timed[b])
         assert timed[8] - timed[16] == both
+
+
+def test_ruled_tiles_follow_the_batch_and_not_its_bucket():
+    # three ResNet-18s, 14 x 14 x 256: the tile for twelve images is not the one for sixteen
+    w = wl.workload("resnet18x3_bf16_b32")
+    with fsb.Ensemble(w["models"], w["out_hw"], wl.IMAGENET_MEAN, wl.IMAGENET_STD, w["precision"], max_batch=16) as ens:
+        ran = {}
+        for b in (12, 16):
+            fsb.fs_profile_enable(ens.handle)
+            ens.infer(list(wl.images_uniform(w["image_seed"], b, *w["in_hw"])), want_logits=False)
+            ran[b] = {l["kernel"] for l in fsb.fs_profile_launches(ens.handle) if (l["N"], l["K"]) == (256, 2304)}
+            fsb.fs_profile_enable(ens.handle, False)
+            want = {fsb.fs_test_conv_choice(b, 14, 14, 256, 256, 3, 1, 1, fsb.FS_BF16, 3, residual=r)[0] for r in (0, 1)}
+            assert ran[b] == want, b
+        assert ran[12] != ran[16]
