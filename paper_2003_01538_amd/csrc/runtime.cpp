@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <condition_variable>
@@ -694,9 +695,15 @@ void plan_group(fs_ensemble* e, const fs_ensemble_desc* d, Group& g) {
   }
 }
 
+constexpr int kMaxDevices = 64;
+
 int num_cus_of(int dev) {
-  int n = 0;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+  static std::atomic<int> cache[kMaxDevices];  // zeros
+  const bool known = dev >= 0 && dev < kMaxDevices;
+  int n = known ? cache[dev].load(std::memory_order_relaxed) : 0;
+  if (n > 0) return n;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
+  if (known) cache[dev].store(n, std::memory_order_relaxed);
   return n;
 }
 
@@ -1621,7 +1628,6 @@ void pack_images_staged(const fs_image* imgs, int b0, int nb, uint8_t* dst, Imag
 constexpr size_t kNoallocScratchFloats = (size_t)FS_NOALLOC_SCRATCH_BYTES / 4;
 static __device__ __align__(256) float scratch[kNoallocScratchFloats];
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 float* g_scratch_ptr[kMaxDevices] = {};
 
@@ -1636,6 +1642,26 @@ float* noalloc_scratch(int dev) {
     g_scratch_ptr[dev] = static_cast<float*>(p);
   }
   return g_scratch_ptr[dev];
+}
+
+// The kernel of a layer whose caller has the packed weights only; sets a.split.
+// A shape whose reduction the implicit GEMM splits over workgroups is taken only
+// if its partial sums fit the scratch array, whichever kernel then runs it: what
+// the entry point accepts does not follow the kernels.
+int noalloc_tile(ConvArgs& a, int cus) {
+  a.split = conv_split(BF16, a, cus);
+  if (a.split > 1 && conv_partial_floats(a) > kNoallocScratchFloats)
+    fail(FS_ERR_UNSUPPORTED, "the split-K partial sums of this shape (" + std::to_string(conv_partial_floats(a) * 4) +
+                                 " bytes) exceed the " + std::to_string(FS_NOALLOC_SCRATCH_BYTES) + "-byte scratch array");
+  const int few = conv_ks_tile(BF16, a);
+  if (few >= 0) {
+    a.split = 1;
+    return few;
+  }
+  const int t = conv_pick_tile(BF16, a, cus, false);  // the implicit GEMM's tile for the split that it gets
+  if (t < 0 || !conv_tile_ok(BF16, t, a)) fail(FS_ERR_UNSUPPORTED, "no conv kernel takes this shape");
+  if (!conv_tile_direct(conv_tile(BF16, t))) a.split = 1;
+  return t;
 }
 
 }  // namespace
@@ -1663,25 +1689,8 @@ fs_status fs_conv_bf16_device_noalloc(const void* d_in, int32_t B, int32_t H, in
     a.B = B; a.H = H; a.W = W; a.Cin = Cin; a.Ho = Ho; a.Wo = Wo; a.Cout = Cout;
     a.kh = kh; a.kw = kw; a.stride = stride; a.pad = pad; a.relu = relu ? 1 : 0;
     a.K = kh * kw * Cin; a.Kp = a.K; a.M = B * Ho * Wo; a.Z = 1;
-    const int cus = num_cus_of(dev);
-    // a shape whose reduction the implicit GEMM splits over workgroups is
-    // taken only if its partial sums fit the scratch array, whichever kernel
-    // then runs it: what the entry point accepts does not follow the kernels
-    const int tg = conv_pick_tile(BF16, a, cus, false);
-    if (tg < 0 || !conv_tile_ok(BF16, tg, a)) fail(FS_ERR_UNSUPPORTED, "no conv kernel takes this shape");
-    int tl = tg;
-    if (conv_tile_direct(conv_tile(BF16, tg))) {
-      a.split = conv_split(BF16, a, cus);
-      if (a.split > 1) {
-        if (conv_partial_floats(a) > kNoallocScratchFloats)
-          fail(FS_ERR_UNSUPPORTED, "the split-K partial sums of this shape (" +
-                                       std::to_string(conv_partial_floats(a) * 4) + " bytes) exceed the " +
-                                       std::to_string(FS_NOALLOC_SCRATCH_BYTES) + "-byte scratch array");
-        a.partial = noalloc_scratch(dev);
-      }
-    }
-    const int few = conv_ks_tile(BF16, a);
-    if (few >= 0) tl = few;
+    const int tl = noalloc_tile(a, num_cus_of(dev));
+    if (a.split > 1) a.partial = noalloc_scratch(dev);
     launch_conv(a, BF16, tl, static_cast<hipStream_t>(stream));
     HIPCHK(hipGetLastError());
   });
@@ -2225,6 +2234,7 @@ static void run_test_conv(const float* in, int32_t B, int32_t H, int32_t W, int3
     if (tl < 0) {  // as the allocation-free entry point, whose caller has packed weights only
       ConvArgs q = a;
       q.wf = nullptr;
+      q.split = conv_split(p, q, num_cus_of(device));
       tl = conv_pick_tile(p, q, num_cus_of(device));
     }
     if (!conv_tile_ok(p, tl, a)) fail(FS_ERR_UNSUPPORTED, "tile " + std::to_string(tile) + " does not fit this conv");
@@ -2264,9 +2274,14 @@ fs_status fs_test_conv_choice(int32_t B, int32_t H, int32_t W, int32_t Cin, int3
     a.K = kh * kw * a.Cin; a.Kp = (int)round_up(a.K, CONV_KPAD); a.M = B * a.Ho * a.Wo; a.Z = Z;
     if (!packed && conv_frag_wanted(p, Cout, a.Kp)) a.wf = &a;  // only asked whether they are there
     if (residual) a.res = &a;
-    a.split = conv_split(p, a, num_cus);
-    *tile = conv_pick_tile(p, a, num_cus);
-    if (*tile < 0 || !conv_tile_ok(p, *tile, a)) fail(FS_ERR_UNSUPPORTED, "no conv kernel takes this shape");
+    if (packed) {
+      if (p != BF16 || Z != 1) fail(FS_ERR_INVALID, "packed weights only: bf16 and one model");
+      *tile = noalloc_tile(a, num_cus);
+    } else {
+      a.split = conv_split(p, a, num_cus);
+      *tile = conv_pick_tile(p, a, num_cus);
+      if (*tile < 0 || !conv_tile_ok(p, *tile, a)) fail(FS_ERR_UNSUPPORTED, "no conv kernel takes this shape");
+    }
     *split = conv_tile_direct(conv_tile(p, *tile)) ? a.split : 1;
   });
 }
@@ -2540,10 +2555,16 @@ fs_status fs_bench_conv(int32_t B, int32_t H, int32_t W, int32_t Cin, int32_t Co
     a.B = B; a.H = gH; a.W = gW; a.Cin = gC; a.Ho = Ho; a.Wo = Wo; a.Cout = Cout;
     a.kh = gk; a.kw = gk; a.stride = gs; a.pad = gp; a.relu = relu ? 1 : 0;
     a.K = K; a.Kp = Kp; a.M = B * Ho * Wo; a.Z = Z;
-    int tl = tile < 0 ? conv_pick_tile(p, a, num_cus_of(device)) : tile;
+    const int split = conv_split(p, a, num_cus_of(device));
+    int tl = tile;
+    if (tl < 0) {
+      a.split = split;
+      tl = conv_pick_tile(p, a, num_cus_of(device));
+      a.split = 1;
+    }
     if (!conv_tile_ok(p, tl, a)) fail(FS_ERR_UNSUPPORTED, "tile does not fit this conv");
     if (conv_tile_direct(conv_tile(p, tl))) {
-      a.split = conv_split(p, a, num_cus_of(device));
+      a.split = split;
       if (a.split > 1) a.partial = static_cast<float*>(t.alloc(conv_partial_floats(a) * 4));
     }
     if (tile_used) *tile_used = tl;

@@ -54,3 +54,17 @@ def test_the_split_reduction_kernel_takes_the_layers_it_is_faster_on(B, hw, cin,
                                                                      split):
     name, _ = fsb.fs_test_conv_choice(B, hw, hw, cin, cout, k, stride, k // 2, fsb.FS_BF16, Z, packed, residual)
     assert ("ks_" in name) == split, name
+
+
+def test_the_allocation_free_call_costs_a_split_layer_as_it_runs():
+    # in four splits: 64x128 tiles 20.0 us, 64x64, the choice for the unsplit layer, 21.0
+    assert fsb.fs_test_conv_choice(25, 7, 10, 2048, 512, 1, 1, 0, fsb.FS_BF16, 1, packed=True) == \
+        ("bf16dma2_64x128_w4_v8", 4)
+
+
+def test_the_allocation_free_call_accepts_by_its_scratch():
+    # few tiles, so that no partial sums would be written; what is accepted does not follow the kernel
+    with pytest.raises(fsb.FsError) as e:
+        fsb.fs_test_conv_choice(5, 16, 16, 256, 1216, 3, 1, 1, fsb.FS_BF16, 1, packed=True)
+    assert e.value.status == fsb.FS_ERR_UNSUPPORTED
+    assert fsb.fs_test_conv_choice(5, 16, 16, 256, 1216, 3, 1, 1, fsb.FS_BF16, 1)[0]
