@@ -524,11 +524,12 @@ int conv_ks_pick(const ConvArgs& a_in, int* bm, int* bn) {
     if (!conv_ks_ok(a, kKsTiles[i].bm, kKsTiles[i].bn)) continue;
     bool rounds = false;
     const double e = ks_estimate(a, kKsTiles[i], cus, &rounds);
-    // in a network, whose weights are not in L2 again when a launch starts, more
-    // workgroups cost more than in a loop: of nearly equal tiles the larger one
-    // (14x14x256, B = 32: 64x64 12.5 us in a loop and 15.4 among the other
-    // layers, 64x128 12.4 and 14.4)
-    const double key = rounds && a.wf ? 1.05 * e : e;
+    // of nearly equal tiles the larger one: more workgroups cost more than the
+    // estimate where their weights are not in L2 again when a launch starts
+    // (14x14x256, B = 32, among the layers of a network: 64x64 15.4 us, 64x128
+    // 14.4, in a loop 12.5 and 12.4) or have to be turned (16x16x256, B = 24: 18.9
+    // and 16.1)
+    const double key = rounds ? 1.05 * e : e;
     if (key < best) {
       best = key;
       us = e;

@@ -68,3 +68,9 @@ def test_the_allocation_free_call_accepts_by_its_scratch():
         fsb.fs_test_conv_choice(5, 16, 16, 256, 1216, 3, 1, 1, fsb.FS_BF16, 1, packed=True)
     assert e.value.status == fsb.FS_ERR_UNSUPPORTED
     assert fsb.fs_test_conv_choice(5, 16, 16, 256, 1216, 3, 1, 1, fsb.FS_BF16, 1)[0]
+
+
+@pytest.mark.parametrize("B,hw,packed", [(24, 16, True), (32, 14, False)])
+def test_of_nearly_equal_tiles_the_larger_one(B, hw, packed):
+    name, _ = fsb.fs_test_conv_choice(B, hw, hw, 256, 256, 3, 1, 1, fsb.FS_BF16, 1, packed)
+    assert name == "bf16ks_64x128_w8_v8", name
