@@ -3,7 +3,7 @@
 // ReLU) of the block after it, which reads the first one's output.
 //
 // Both are bound by memory: of the traffic of the two launches (64 -> 256
-// channels with a residual, then 256 -> 64: 832 channels per pixel) a third
+// channels with a residual, then 256 -> 64: 896 channels per pixel) more than a quarter
 // is the wide tensor, written by the first and read again by the second.  It
 // still has to be written - the block after next takes it as its residual -
 // but need not be read: the MFMA leaves a lane eight consecutive channels of
@@ -61,7 +61,7 @@ __global__ void __launch_bounds__(256, OCC) k_conv_pair(ConvArgs a, ConvArgs d) 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   // Read as floatx4 below: before a read of LDS that it cannot tell from the
   // direct loads by type, the compiler waits for every one in flight.
-  __shared__ float sb1[MAXN1 + NB2 * 32];
+  __shared__ __attribute__((aligned(16))) float sb1[MAXN1 + NB2 * 32];
   float* const sb2 = sb1 + MAXN1;
 
   const int tid = threadIdx.x, lane = tid & 63, fq = lane >> 5;

@@ -225,3 +225,18 @@ def test_streamed_weight_halo_kernel_uses_lds_reads_only_after_their_wait():
     for f, lines in kernels.items():
         found = lds_hazards_cfg(lines)
         assert not found, f"{f}: {len(found)} uses before the wait, first {found[:3]}"
+
+
+def test_lds_arrays_that_are_read_sixteen_bytes_at_a_time_state_their_alignment():
+    # a plain float array is aligned to four bytes by its type; that the compiler
+    # places it on sixteen is no promise
+    found = []
+    for f in sorted(os.listdir(CSRC)):
+        if not f.endswith((".hip", ".hpp")):
+            continue
+        src = open(os.path.join(CSRC, f)).read()
+        for m in re.finditer(r"__shared__ (?!__attribute__)(\w+) (\w+)\[", src):
+            if m.group(1) != "floatx4" and re.search(
+                    r"reinterpret_cast<(?:const )?(?:float4|floatx4|uint4|bf16x8)\*>\(&?" + m.group(2) + r"\b", src):
+                found.append((f, m.group(2)))
+    assert not found, found
