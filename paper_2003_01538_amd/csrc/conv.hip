@@ -49,9 +49,7 @@ __device__ __forceinline__ typename VecT<BYTES>::T buf_load(__amdgpu_buffer_rsrc
     return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
 }
 
-// FAST: Cin is a multiple of BK, so every K-tile lies inside one filter tap
-// (ky, kx) and a contiguous channel range: the tap is wave-uniform.
-template <int BM, int BN, int VEC, bool FAST>
+template <int BM, int BN, int VEC>
 __global__ void __launch_bounds__(NT, BM >= 256 ? 1 : 2) k_conv(ConvArgs a) {
   using T = uint16_t;
   constexpr int BK = 64, KSTEP = 32;
@@ -131,21 +129,11 @@ __global__ void __launch_bounds__(NT, BM >= 256 ? 1 : 2) k_conv(ConvArgs a) {
   AV ra0[AP], ra1[AP];
   uint4 rb0[BP], rb1[BP];
   auto load_tiles = [&](AV* ra, uint4* rb, int kt) {
-    int tky, tkx, tci;
-    if constexpr (FAST) {  // wave-uniform tap of this K-tile
-      const int k0 = kt * BK;
-      const int tap = k0 / a.Cin;
-      tci = k0 - tap * a.Cin;
-      tky = tap / a.kw;
-      tkx = tap - tky * a.kw;
-    } else {
-      tky = ky; tkx = kx; tci = ci - aj * VEC;
-    }
-    const bool kvalid = tky < a.kh;
-    const int tap_off = (tky * a.W + tkx) * a.Cin + tci;
+    const bool kvalid = ky < a.kh;
+    const int tap_off = (ky * a.W + kx) * a.Cin + ci - aj * VEC;
 #pragma unroll
     for (int p = 0; p < AP; ++p) {
-      const int iy = a_iy[p] + tky, ix = a_ix[p] + tkx;
+      const int iy = a_iy[p] + ky, ix = a_ix[p] + kx;
       const bool ok = kvalid && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
       ra[p] = buf_load<AVB>(rx, ok ? (uint32_t)((a_off[p] + tap_off) * ES) : OOB);
     }
@@ -154,12 +142,10 @@ __global__ void __launch_bounds__(NT, BM >= 256 ? 1 : 2) k_conv(ConvArgs a) {
       rb[p] = buf_load<16>(rw, b_off[p] == OOB ? OOB : b_off[p] + (uint32_t)(kt * BK * ES));
   };
   auto advance_k = [&]() {
-    if constexpr (!FAST) {
-      ci += BK;
-      while (ci >= a.Cin) {
-        ci -= a.Cin;
-        if (++kx == a.kw) { kx = 0; ++ky; }
-      }
+    ci += BK;
+    while (ci >= a.Cin) {
+      ci -= a.Cin;
+      if (++kx == a.kw) { kx = 0; ++ky; }
     }
   };
   auto store_tiles = [&](int buf, const AV* ra, const uint4* rb) {
@@ -433,10 +419,7 @@ int conv_pick_tile(Prec p, const ConvArgs& a, int num_cus, bool ks) {
 template <int BM, int BN, int VEC>
 static void launch_t(const ConvArgs& a, hipStream_t s) {
   const int tiles = ((a.M + BM - 1) / BM) * ((a.Cout + BN - 1) / BN) * a.Z;
-  if (a.Cin % 64 == 0)
-    hipLaunchKernelGGL((k_conv<BM, BN, VEC, true>), dim3(tiles), dim3(NT), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_conv<BM, BN, VEC, false>), dim3(tiles), dim3(NT), 0, s, a);
+  hipLaunchKernelGGL((k_conv<BM, BN, VEC>), dim3(tiles), dim3(NT), 0, s, a);
 }
 
 void launch_conv(const ConvArgs& a, Prec p, int tile, hipStream_t s, bool reduce) {
