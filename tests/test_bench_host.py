@@ -25,3 +25,22 @@ def test_traffic_is_withheld_when_the_sources_changed(monkeypatch):
 def test_traffic_is_withheld_without_a_summary(monkeypatch, tmp_path):
     monkeypatch.setattr(bench, "PROFILE", str(tmp_path / "missing.md"))
     assert bench.counted_traffic() is None
+
+
+def test_the_source_hash_covers_every_conv_source(monkeypatch):
+    import hashlib
+    seen = []
+
+    class Recorder:
+        def update(self, data):
+            seen.append(data)
+
+        def hexdigest(self):
+            return "0" * 64
+
+    monkeypatch.setattr(hashlib, "sha256", Recorder)
+    bench.conv_source_hash()
+    csrc = os.path.join(ROOT, "paper_2003_01538_amd", "csrc")
+    for f in sorted(os.listdir(csrc)):
+        if (f.startswith("conv") and f.endswith(".hip")) or f == "lds_dma.hpp":
+            assert open(os.path.join(csrc, f), "rb").read() in seen, f
