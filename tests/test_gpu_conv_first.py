@@ -1,6 +1,6 @@
 """A network's first 3x3 convolution fused with its 2x2 max pool: against the
-CPU oracle and the two layers run separately, at sizes around the eight
-windows a wave takes at a time and the four rows of a workgroup."""
+CPU oracle and the two layers run separately, at sizes around the run of 32
+windows that a wave takes at a time, and with more runs than waves."""
 import numpy as np
 import pytest
 
@@ -11,7 +11,9 @@ from tests.test_gpu_kernels import BF16, assert_bf16_close
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,H,W", [(1, 2, 2), (2, 6, 16), (3, 10, 18), (1, 34, 14), (5, 18, 66), (1, 224, 224)])
+@pytest.mark.parametrize("B,H,W", [(1, 2, 2), (2, 6, 16), (3, 10, 18), (1, 34, 14), (5, 18, 66), (1, 224, 224),
+                                   (1, 2, 66), (1, 6, 42),   # 33 windows and 63: one and thirty-one in the last run
+                                   (5, 202, 278)])           # 2194 runs: a second one a wave, whose step crosses rows and images
 def test_first_conv_maxpool_fused(gpu_lib, B, H, W):
     rng = np.random.default_rng(H * 1000 + W)
     x = oracle.round_bf16(rng.standard_normal((B, H, W, 3)).astype(np.float32))
