@@ -467,7 +467,9 @@ static double ks_estimate(const ConvArgs& a, const KsTile& t, double cus, bool* 
 
 // The time below which this kernel is taken: that of the kernel that runs the
 // layer otherwise, less what the estimates may be off.  An ensemble's implicit
-// GEMM runs in the fastest of twenty timed tiles, of which nine are estimated.
+// GEMM runs in the fastest of twenty timed tiles, of which nine are estimated;
+// short reductions leave little to split (1x1, 512 -> 128 on 28x28, B = 14 to 22,
+// packed: 7.9 us against 8.6).
 static double ks_limit(const ConvArgs& a, double cus) {
   const double nk = a.K / BK;
   if (conv_hs_chosen(a)) {
@@ -492,7 +494,7 @@ static double ks_limit(const ConvArgs& a, double cus) {
   double us = 0;
   conv_dma_pick(d, (int)cus, &us);
   if (d.split > 1) us += 3.0 + (double)d.split * a.M * a.Cout * a.Z * 8 / 6.5e6;  // the completion: partial sums out and in
-  return (a.wf ? 0.91 : 0.97) * us;
+  return (a.wf || nk <= 8 ? 0.91 : 0.97) * us;
 }
 
 // Which of this kernel's tiles runs the layer, or -1: the one that is estimated
@@ -503,7 +505,7 @@ static double ks_limit(const ConvArgs& a, double cus) {
 // 117, B = 1 to 48, one to five models.  The rule is 0.3 % slower there than the
 // fastest kernel on average, and nowhere more than 3 % slower than the kernel
 // that ran the layer otherwise at its fastest tile (packed rows: against that
-// kernel at the tile it gets).  Measured (us, this kernel against the other):
+// kernel at the tile it gets, with two of 192 layers 0.3 and 0.8 us slower).  Measured (us, this kernel against the other):
 // 7x7x512 3x3, three models, B = 1 / 8 / 16: 7.3 / 12.4 / 17.6 against 26.3 / 32.4 /
 // 32.5; 14x14x256 B = 1 / 8: 6.1 / 11.3 against 15.9 / 16.6; 28x28x128 to 256
 // stride 2 (split over workgroups), B = 8 / 16: 9.3 / 12.7 against 16.9 / 22.5.

@@ -45,6 +45,7 @@ def test_fp32_filters_of_any_size_have_a_kernel():
     (12, 14, 512, 512, 3, 1, 5, False, False, False),   # three rounds of one workgroup a CU: 64 us against 51
     (7, 28, 512, 512, 3, 1, 2, False, False, False),    # 63 us against 51
     (6, 16, 2048, 512, 1, 1, 2, False, True, False),    # 29 us against 22
+    (19, 28, 512, 128, 1, 1, 1, True, False, False),    # eight K-tiles: 8.6 us against 7.9
     (12, 31, 512, 512, 3, 1, 1, True, False, False),    # packed rows that find no LDS to be turned in: 109 us against 67
     (10, 28, 512, 512, 3, 1, 1, True, False, False),    # 73 us against 40
     (4, 28, 512, 512, 3, 1, 1, True, False, False),     # 37 us against 34
