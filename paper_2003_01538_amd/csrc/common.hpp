@@ -79,10 +79,10 @@ struct ConvTile {
 // produce bit-identical sums.
 inline bool conv_tile_direct(const ConvTile& c) { return c.dma > 0; }
 // Kernel family of a tile: 4 reduction split over a workgroup's waves (one
-// tile, by rule; never timed), 3 halo with streamed weights, 2 halo with resident
-// weights, 1 LDS-DMA implicit GEMM, 0 register-staged implicit GEMM.  A layer
-// always runs in the highest family that fits it, and tiles are only ever
-// compared within one family.
+// tile, by a rule on shape and batch; never timed), 3 halo with streamed weights,
+// 2 halo with resident weights, 1 LDS-DMA implicit GEMM, 0 register-staged
+// implicit GEMM.  A layer always runs in the highest family that takes it, and
+// tiles are only ever compared within one family.
 inline int conv_tile_family(const ConvTile& c) {
   return c.halo == 4 ? 4 : c.halo >= 2 ? 3 : c.halo ? 2 : (c.dma > 0 ? 1 : 0);
 }
